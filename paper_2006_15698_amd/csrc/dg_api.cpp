@@ -87,50 +87,91 @@ const double kRKB[5] = {1432997174477.0 / 9575080441755.0,
                         2277821191437.0 / 14882151754819.0};
 
 // Legendre P_n(x) and P_n'(x) by the three-term recurrence.
-void legendre(int n, double x, double* pn, double* dpn) {
-  double p0 = 1.0, p1 = x;
+template <class T>
+void legendre(int n, T x, T* pn, T* dpn) {
+  T p0 = 1, p1 = x;
   if (n == 0) {
-    *pn = 1.0;
-    *dpn = 0.0;
+    *pn = 1;
+    *dpn = 0;
     return;
   }
   for (int k = 2; k <= n; ++k) {
-    const double p2 = ((2.0 * k - 1.0) * x * p1 - (k - 1.0) * p0) / k;
+    const T p2 = ((T(2) * k - T(1)) * x * p1 - (k - T(1)) * p0) / k;
     p0 = p1;
     p1 = p2;
   }
   *pn = p1;
-  *dpn = n * (x * p1 - p0) / (x * x - 1.0);
+  *dpn = n * (x * p1 - p0) / (x * x - T(1));
 }
 
 // N-point Gauss-Legendre rule (Section II-B): Newton iteration on P_N from
 // Chebyshev-like initial guesses, weights 2 / ((1 - x^2) P_N'(x)^2).
-void gauss_legendre(int n, double* x, double* w) {
+template <class T>
+void gauss_legendre(int n, T* x, T* w) {
+  const T tol = sizeof(T) > sizeof(double) ? T(1e-19L) : T(1e-17);
   for (int i = 0; i < n; ++i) {
-    double z = -std::cos(M_PI * (i + 0.75) / (n + 0.5));
+    T z = -std::cos(M_PI * (i + 0.75) / (n + 0.5));
     for (int it = 0; it < 100; ++it) {
-      double pn, dpn;
+      T pn, dpn;
       legendre(n, z, &pn, &dpn);
-      const double dz = pn / dpn;
+      const T dz = pn / dpn;
       z -= dz;
-      if (std::fabs(dz) < 1e-17) break;
+      if (std::fabs(dz) < tol) break;
     }
-    double pn, dpn;
+    T pn, dpn;
     legendre(n, z, &pn, &dpn);
     x[i] = z;
-    w[i] = 2.0 / ((1.0 - z * z) * dpn * dpn);
+    w[i] = T(2) / ((T(1) - z * z) * dpn * dpn);
   }
-  if (n % 2 == 1) x[n / 2] = 0.0;  // exact centre node for odd n
+  if (n % 2 == 1) x[n / 2] = 0;  // exact centre node for odd n
   // enforce the symmetry of the rule
   for (int i = 0; i < n / 2; ++i) {
-    const double xs = 0.5 * (x[n - 1 - i] - x[i]);
-    const double ws = 0.5 * (w[n - 1 - i] + w[i]);
+    const T xs = T(0.5) * (x[n - 1 - i] - x[i]);
+    const T ws = T(0.5) * (w[n - 1 - i] + w[i]);
     x[i] = -xs;
     x[n - 1 - i] = xs;
     w[i] = ws;
     w[n - 1 - i] = ws;
   }
 }
+
+// The rule and the one-dimensional operators on it, in precision T.
+template <class T>
+struct Line1D {
+  T x[DG_MAXN], w[DG_MAXN], lm[DG_MAXN], lp[DG_MAXN], Dh[DG_MAXN * DG_MAXN];
+  explicit Line1D(int N) {
+    gauss_legendre(N, x, w);
+    // barycentric weights 1 / prod_{m != i} (xi_i - xi_m)
+    T bw[DG_MAXN];
+    for (int i = 0; i < N; ++i) {
+      T prod = 1;
+      for (int m = 0; m < N; ++m)
+        if (m != i) prod *= (x[i] - x[m]);
+      bw[i] = T(1) / prod;
+    }
+    // D[a][i] = l_i'(xi_a): off-diagonal (bw_i / bw_a) / (xi_a - xi_i),
+    // diagonal from the zero row sum (derivative of a constant).
+    T D[DG_MAXN][DG_MAXN];
+    for (int a = 0; a < N; ++a) {
+      T s = 0;
+      for (int i = 0; i < N; ++i) {
+        if (i == a) continue;
+        D[a][i] = (bw[i] / bw[a]) / (x[a] - x[i]);
+        s += D[a][i];
+      }
+      D[a][a] = -s;
+    }
+    for (int i = 0; i < N; ++i) {
+      lm[i] = lp[i] = 1;
+      for (int m = 0; m < N; ++m) {
+        if (m == i) continue;
+        lm[i] *= (T(-1) - x[m]) / (x[i] - x[m]);
+        lp[i] *= (T(1) - x[m]) / (x[i] - x[m]);
+      }
+      for (int a = 0; a < N; ++a) Dh[i * N + a] = w[a] * D[a][i] / w[i];
+    }
+  }
+};
 
 void build_tables(dg_ctx* c) {
   dg_build_tables(c->nx, c->ny, c->nz, c->p, c->gamma, c->L, &c->tab, c->xi, c->w);
@@ -332,50 +373,39 @@ void dg_build_tables(int nx, int ny, int nz, int p, double gamma, const double L
   const int N = p + 1;
   DGTables& t = *tp;
   std::memset(&t, 0, sizeof(t));
-  gauss_legendre(N, xi, w);
-  // barycentric weights 1 / prod_{m != i} (xi_i - xi_m)
-  double bw[DG_MAXN];
+  // The FP64 tables: worked out in extended precision, so that each is within
+  // an ulp of its exact value, and with the rule's reflection symmetry,
+  // l_i(1) = l_{N-1-i}(-1) and l_i'(xi_a) = -l_{N-1-i}'(-xi_a), to the last
+  // bit, so that a kernel may hold half of a table.
+  const Line1D<long double> e(N);
   for (int i = 0; i < N; ++i) {
-    double prod = 1.0;
-    for (int m = 0; m < N; ++m)
-      if (m != i) prod *= (xi[i] - xi[m]);
-    bw[i] = 1.0 / prod;
-  }
-  // D[a][i] = l_i'(xi_a): off-diagonal (bw_i / bw_a) / (xi_a - xi_i),
-  // diagonal from the zero row sum (derivative of a constant).
-  double D[DG_MAXN][DG_MAXN];
-  for (int a = 0; a < N; ++a) {
-    double s = 0.0;
-    for (int i = 0; i < N; ++i) {
-      if (i == a) continue;
-      D[a][i] = (bw[i] / bw[a]) / (xi[a] - xi[i]);
-      s += D[a][i];
-    }
-    D[a][a] = -s;
-  }
-  for (int i = 0; i < N; ++i) {
-    double lm = 1.0, lp = 1.0;
-    for (int m = 0; m < N; ++m) {
-      if (m == i) continue;
-      lm *= (-1.0 - xi[m]) / (xi[i] - xi[m]);
-      lp *= (1.0 - xi[m]) / (xi[i] - xi[m]);
-    }
-    t.lm[i] = lm;
-    t.lp[i] = lp;
-    t.liftm[i] = lm / w[i];
-    t.liftp[i] = lp / w[i];
+    xi[i] = (double)e.x[i];
+    w[i] = (double)e.w[i];
     t.w[i] = w[i];
-    for (int a = 0; a < N; ++a) t.Dh[i * N + a] = w[a] * D[a][i] / w[i];
+    t.lm[i] = (double)e.lm[i];
+    t.lp[i] = (double)e.lm[N - 1 - i];
+    t.liftm[i] = (double)(e.lm[i] / e.w[i]);
+    t.liftp[i] = (double)(e.lm[N - 1 - i] / e.w[N - 1 - i]);
   }
+  for (int k = 0; k < N * N / 2; ++k) {
+    t.Dh[k] = (double)e.Dh[k];
+    t.Dh[N * N - 1 - k] = -t.Dh[k];
+  }
+  if (N % 2 == 1) t.Dh[N * N / 2] = 0.0;
+  // The FP32 form's: worked out in double (its FP32 roundings would carry an
+  // ulp's change of a table through the deviations).
+  const Line1D<double> d(N);
   for (int i = 0; i < N; ++i) {
     double s = 0.0;
     for (int a = 0; a < N; ++a) {
-      s += t.Dh[i * N + a];
-      t.Dh32[i * N + a] = (float)t.Dh[i * N + a];
+      s += d.Dh[i * N + a];
+      t.Dh32[i * N + a] = (float)d.Dh[i * N + a];
     }
     t.rs[i] = s;
-    t.lm32[i] = (float)t.lm[i];
-    t.lp32[i] = (float)t.lp[i];
+    t.lm32[i] = (float)d.lm[i];
+    t.lp32[i] = (float)d.lp[i];
+    t.liftm32[i] = d.lm[i] / d.w[i];
+    t.liftp32[i] = d.lp[i] / d.w[i];
   }
   const double h[3] = {L[0] / nx, L[1] / ny, L[2] / nz};
   for (int d = 0; d < 3; ++d) {
@@ -669,7 +699,12 @@ int64_t dg_num_dof(const dg_ctx* c) {
 int dg_quadrature(int p, double* xi, double* w) {
   if (p < 0 || p >= DG_MAXN) return fail(DG_EUNSUPPORTED, "p must be in 0..%d", DG_MAXN - 1);
   if (!xi || !w) return fail(DG_EINVAL, "NULL output");
-  gauss_legendre(p + 1, xi, w);
+  long double x[DG_MAXN], wl[DG_MAXN];
+  gauss_legendre(p + 1, x, wl);
+  for (int i = 0; i <= p; ++i) {
+    xi[i] = (double)x[i];
+    w[i] = (double)wl[i];
+  }
   return DG_OK;
 }
 

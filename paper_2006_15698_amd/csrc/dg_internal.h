@@ -25,6 +25,8 @@ struct DGTables {
   float Dh32[DG_MAXN * DG_MAXN]; // Dh rounded to FP32 (matrix-core variant)
   float lm32[DG_MAXN];           // l_i(-1), l_i(+1) rounded to FP32
   float lp32[DG_MAXN];
+  double liftm32[DG_MAXN];       // the FP32 form's lift weights (FP64)
+  double liftp32[DG_MAXN];
   double sc[3];                  // 2 / h_d (reference-to-physical metric)
   double hinv[3];                // 1 / h_d
   double J;                      // h_x h_y h_z / 8 (volume Jacobian)

@@ -172,8 +172,8 @@ __device__ __forceinline__ void stage_body32(const DGTables& tb, double* __restr
   if (tid < N) {
     sLm[tid] = tb.lm32[tid];
     sLp[tid] = tb.lp32[tid];
-    sLiftm[tid] = tb.liftm[tid];
-    sLiftp[tid] = tb.liftp[tid];
+    sLiftm[tid] = tb.liftm32[tid];
+    sLiftp[tid] = tb.liftp32[tid];
     sRs[tid] = tb.rs[tid];
   }
 

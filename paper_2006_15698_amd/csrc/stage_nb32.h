@@ -240,8 +240,8 @@ __device__ __forceinline__ void stage_nb32_body(const DGTables& tb, const double
     for (int m = 0; m < N; ++m) {
       a = tid == m ? tb.lm32[m] : a;
       b = tid == m ? tb.lp32[m] : b;
-      c = tid == m ? tb.liftm[m] : c;
-      d = tid == m ? tb.liftp[m] : d;
+      c = tid == m ? tb.liftm32[m] : c;
+      d = tid == m ? tb.liftp32[m] : d;
       e = tid == m ? tb.rs[m] : e;
     }
     sLm[tid] = a;
