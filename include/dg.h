@@ -148,10 +148,13 @@ int dg_set_volume_form(dg_ctx* ctx, int form);
  *   (ragged pencils and rows are handled).
  * DG_OPT_PENCIL_X: elements of a pencil along x (rounded up to the
  *   kernel's block of elements; 0 = the whole row).
- * DG_OPT_PENCIL_Z: element planes of a pencil along z (>= 1).
+ * DG_OPT_PENCIL_Z: element planes of a pencil along z (>= 1).  Until it is
+ *   set, with DG_OPT_XCD_REMAP on, pencils are fewer planes deep where the
+ *   arrays of a stage exceed the last-level cache.
  * DG_OPT_XCD_REMAP: 1 gives each of the 8 XCDs of the MI355X (each with
- *   its own L2) a contiguous part of the visiting order; 0 leaves the
- *   hardware's round-robin spread of workgroups over the XCDs.
+ *   its own L2) a contiguous part of the visiting order, or of every z-slab
+ *   of PENCIL_Z planes; 0 leaves the hardware's round-robin spread of
+ *   workgroups over the XCDs.
  * DG_OPT_VISC_FUSED: with viscosity set (FP64, standard volume form), 1
  *   forms the inviscid rate inside the viscous-flux launch from the
  *   neighbour loads that launch makes anyway; 0 gives it a launch of its

@@ -497,12 +497,13 @@ dg_ctx* dg_create(int nx, int ny, int nz, int p, double gamma) {
   c->stream = nullptr;
   c->precision = DG_FP64;
   c->exchange = DG_EXCHANGE_NEIGHBOUR;
-  // Fastest measured on MI355X (32^3 p=3, 48^3 p=4, 40^3 p=6): pencils of
-  // 16 x 8 elements, each XCD taking a contiguous part of the order.
+  // Pencils of 16 x 8 elements (one plane deep where the arrays stream from
+  // HBM, dg_order), the XCDs sharing every slab.
   c->order = DG_ORDER_PENCIL;
   c->xcd_remap = 1;
   c->pencil_x = 16;
   c->pencil_z = 8;
+  c->pencil_z_set = 0;
   c->visc_fused = 1;
   c->mu = 0.0;
   c->prandtl = 0.72;
@@ -650,6 +651,7 @@ int dg_set_option(dg_ctx* c, int key, int value) {
   if (key == DG_OPT_PENCIL_Z) {
     if (value < 1) return fail(DG_EINVAL, "pencil z extent %d < 1", value);
     c->pencil_z = value;
+    c->pencil_z_set = 1;
     ++c->epoch;
     return DG_OK;
   }

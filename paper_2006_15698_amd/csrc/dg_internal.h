@@ -54,6 +54,7 @@ struct dg_ctx {
   int order;      // DG_ORDER_LINEAR or DG_ORDER_PENCIL
   int pencil_x;   // pencil extent along x in elements (0: whole row)
   int pencil_z;   // pencil extent along z in element planes
+  int pencil_z_set;  // pencil_z was chosen by the caller (dg_order)
   int visc_fused; // viscous FP64 standard form: inviscid rate inside the viscous-flux launch
   // viscous terms (dg_set_viscosity): dynamic viscosity, Prandtl number and
   // conductivity mu gamma / ((gamma - 1) Pr); mu = 0 is the Euler equations
@@ -72,6 +73,25 @@ struct dg_ctx {
   unsigned gepoch;
 };
 
+// n / d for 0 <= n < 2^31 by a multiplication: with s = ceil(log2 d) and
+// m = floor(2^32 (2^s - d) / d) + 1 the quotient is (mulhi(n, m) + n) >> s.
+// (A division costs a wave about 25 dependent instructions, and a block's
+// place in the visiting order takes four of them.)
+struct DGDiv {
+  unsigned m;
+  int s;
+};
+inline DGDiv dg_div(unsigned d) {
+  DGDiv v;
+  v.s = 0;
+  while ((1ull << v.s) < d) ++v.s;
+  v.m = (unsigned)((((1ull << v.s) - d) << 32) / d + 1);
+  return v;
+}
+__host__ __device__ __forceinline__ int dg_quot(int n, DGDiv v) {
+  return (int)(((unsigned)(((unsigned long long)(unsigned)n * v.m) >> 32) + (unsigned)n) >> v.s);
+}
+
 // Order in which a neighbour-read stage launch visits its element blocks
 // (kernel argument).  A block is EPB consecutive elements of one x-row (the
 // last block of a row may be short).  Blocks are visited z-slab by z-slab
@@ -79,23 +99,52 @@ struct dg_ctx {
 // pencil y-row by y-row, and inside that z-plane by z-plane, x fastest.
 // Index order is the special case of whole-row pencils one plane deep.
 struct DGOrder {
-  int xcd;      // chunk the visiting order per XCD
+  int xcd;      // the XCDs share every `share` blocks, each taking a contiguous eighth
   int nxb;      // blocks per x-row
   int tx;       // blocks of a pencil along x
   int tz;       // element planes of a pencil along z
+  int slab;     // blocks of a whole slab
+  int share;    // blocks the XCDs share at a time: a whole slab, or all
+  int full;     // whole shares
+  int q;        // share / 8
+  DGDiv dslab, dq, dpen, drow, dtx;   // by slab, q, and a whole pencil's blocks, blocks per y-row, blocks along x
 };
 
-// Visiting order and grid size of a neighbour-read stage launch with EPB
-// elements per block.
-inline DGOrder dg_order(const dg_ctx* c, int epb, unsigned* grid) {
+// Visiting order and grid size of a neighbour-read launch with EPB elements
+// per block.
+//
+// Where the arrays of a stage (state in and out, residual) exceed the 256 MB
+// last-level cache the XCDs share every slab, and slabs are `planes` deep
+// unless the caller chose a depth: the XCDs then work on the same few planes
+// and the neighbours of their parts come from HBM once.  With an eighth of
+// the whole order each, they were spread over the mesh: k_stage_line 596
+// against 557 us a stage at 48^3 p=4 (one plane; 8 planes 586), 275 against
+// 250 at 48^3 p=3; k_split 950 / 925 (4 planes) at 48^3 p=4; the viscous
+// pair 2166 / 2125; k_stage_nb32 738 / 717.  Within the cache the line kernel
+// shares slabs of 8 planes (32^3 p=3 68 us; of one plane 73), the others
+// keep an eighth of the order each (32^3 p=3 viscous 314, sharing slabs 319).
+inline DGOrder dg_order(const dg_ctx* c, int epb, unsigned* grid, bool line = false) {
   DGOrder o;
   const bool pencil = c->order == DG_ORDER_PENCIL;
+  const int64_t bytes = 3 * DG_NF * (int64_t)sizeof(double) * c->E * c->N * c->N * c->N;
+  const bool hbm = bytes > ((int64_t)256 << 20);
   o.xcd = c->xcd_remap;
   o.nxb = (c->nx + epb - 1) / epb;
   const int px = pencil && c->pencil_x > 0 && c->pencil_x < c->nx ? c->pencil_x : c->nx;
   o.tx = (px + epb - 1) / epb;
-  o.tz = !pencil || c->pencil_z < 1 ? 1 : (c->pencil_z > c->nz ? c->nz : c->pencil_z);
+  o.tz = !pencil || c->pencil_z < 1 ? 1 : c->pencil_z;
+  if (pencil && o.xcd && hbm && !c->pencil_z_set) o.tz = line ? 1 : 4;
+  if (o.tz > c->nz) o.tz = c->nz;
   *grid = (unsigned)((int64_t)o.nxb * c->ny * c->nz);
+  o.slab = o.nxb * c->ny * o.tz;
+  o.share = line || hbm ? o.slab : (int)*grid;
+  o.full = (int)(*grid / (unsigned)o.share);
+  o.q = o.share >> 3;
+  o.dslab = dg_div(o.slab);
+  o.dq = dg_div(o.q > 0 ? o.q : 1);
+  o.dpen = dg_div(c->ny * o.tz * o.tx);
+  o.drow = dg_div(o.tz * o.tx);
+  o.dtx = dg_div(o.tx);
   return o;
 }
 

@@ -22,6 +22,7 @@
 #include "stage_nb32.h"
 #include "stage_fp64.h"
 #include "stage_nb.h"
+#include "stage_line.h"
 
 namespace {
 
@@ -103,47 +104,76 @@ k_batch_stage(const DGBatchInst* __restrict__ inst, const int2* __restrict__ ite
 }
 
 // One (N, EPB) variant over its own items, one workgroup per item
-// (DG_BATCH_PER_DEGREE): the variant's own register allocation and shared
-// memory.  With xcd set, workgroup w takes item xcd_block(w): each XCD a
-// contiguous part of the items.
-template <int N, int EPB, int MODE, bool F32>
+// (DG_BATCH_PER_DEGREE), FP32 contractions: the variant's own register
+// allocation and shared memory.  With xcd set, workgroup w takes item
+// xcd_block(w): each XCD a contiguous part of the items.
+template <int N, int EPB, int MODE>
 __global__ void __launch_bounds__(BNT)
-k_batch_degree(const DGBatchInst* __restrict__ inst, const int2* __restrict__ items, int begin, int xcd,
-               const double* __restrict__ Qin, double* __restrict__ Qout, double* __restrict__ RR, double a,
-               double b, int first) {
-  __shared__ double smem[F32 ? (smax32<N, EPB>() + 7) / 8 : smax64<N, EPB>()];
+k_batch_degree32(const DGBatchInst* __restrict__ inst, const int2* __restrict__ items, int begin, int xcd,
+                 const double* __restrict__ Qin, double* __restrict__ Qout, double* __restrict__ RR, double a,
+                 double b, int first) {
+  __shared__ double smem[(smax32<N, EPB>() + 7) / 8];
   const int w = xcd ? dgdev::xcd_block(blockIdx.x, gridDim.x) : blockIdx.x;
   const int2 it = items[begin + w];
   const int mi = __builtin_amdgcn_readfirstlane(it.x);
   const int e0 = __builtin_amdgcn_readfirstlane(it.y);
   const DGBatchInst& I = inst[mi];
-  const double* qi = Qin + I.qoff;
-  double* qo = Qout ? Qout + I.qoff : nullptr;
-  double* rr = RR + I.qoff;
   const int x0 = e0 % I.tab.nx;
   const int ne = dgdev::imin(EPB, I.tab.nx - x0);
-  if (F32)
-    dgdev::stage_nb32_body<N, MODE, EPB, BNT, dgdev::LINES_POINT>(I.tab, qi, qo, rr, a, b, I.dt, first, e0, ne, smem,
-                                                                  threadIdx.x);
-  else
-    dgdev::stage_nb_body<N, MODE, EPB, BNT, kLines64<N>>(I.tab, qi, qo, rr, a, b, I.dt, first, e0, ne, smem,
-                                                         threadIdx.x);
+  dgdev::stage_nb32_body<N, MODE, EPB, BNT, dgdev::LINES_POINT>(I.tab, Qin + I.qoff, Qout ? Qout + I.qoff : nullptr,
+                                                                RR + I.qoff, a, b, I.dt, first, e0, ne, smem,
+                                                                threadIdx.x);
+}
+
+// The same for FP64: the one-thread-per-line body (stage_line.h), one wave
+// per item, or per part of an item where its lines do not fit one wave
+// (N = 3: 9 elements as 5 + 4).
+template <int N, int EPB>
+struct BatchLine {
+  static constexpr int MAXE = 64 / (N * N);   // elements whose lines fit a wave
+  static constexpr int PARTS = (EPB + MAXE - 1) / MAXE;
+  static constexpr int E = (EPB + PARTS - 1) / PARTS;
+};
+
+template <int N, int EPB, int MODE>
+__global__ void __launch_bounds__(64, 2)
+k_batch_degree(const DGBatchInst* __restrict__ inst, const int2* __restrict__ items, int begin, int xcd,
+               const double* __restrict__ Qin, double* __restrict__ Qout, double* __restrict__ RR, double a,
+               double b, int first) {
+  using BL = BatchLine<N, EPB>;
+  __shared__ __align__(16) double smem[dgdev::LineSmem<N, BL::E>::size];
+  const int w = xcd ? dgdev::xcd_block(blockIdx.x, gridDim.x) : blockIdx.x;
+  const int2 it = items[begin + w / BL::PARTS];
+  const int mi = __builtin_amdgcn_readfirstlane(it.x);
+  const int skip = (w % BL::PARTS) * BL::E;
+  const int e0 = __builtin_amdgcn_readfirstlane(it.y);
+  const DGBatchInst& I = inst[mi];
+  const int row = e0 / I.tab.nx, z = row / I.tab.ny;
+  dgdev::Block blk;
+  blk.x0 = e0 - row * I.tab.nx + skip;
+  blk.y = row - z * I.tab.ny;
+  blk.z = z;
+  blk.e0 = e0 + skip;
+  blk.ne = dgdev::imin(dgdev::imin(BL::E, EPB - skip), I.tab.nx - blk.x0);
+  if (blk.ne <= 0) return;   // the row's last block is short
+  dgdev::stage_line_body<N, MODE, BL::E>(I.tab, Qin + I.qoff, Qout ? Qout + I.qoff : nullptr, RR + I.qoff, a, b,
+                                         I.dt, first, blk, smem, threadIdx.x);
 }
 
 template <int N, int EPB>
 void launch_degree(const DGBatchLaunch& L, int mode, const double* Qin, double* Qout, double* RR, double a, double b,
                    int first) {
-  const dim3 grid((unsigned)L.vcount[N]), blk(BNT);
   const int begin = L.vbegin[N];
-#define DG_LD(m, f)                                                                                               \
-  hipLaunchKernelGGL((k_batch_degree<N, EPB, m, f>), grid, blk, 0, L.stream, L.inst, L.items, begin, L.xcd, Qin, \
-                     Qout, RR, a, b, first)
+#define DG_LD(kernel, m, parts, threads)                                                                            \
+  hipLaunchKernelGGL((kernel<N, EPB, m>), dim3((unsigned)(L.vcount[N] * (parts))), dim3(threads), 0, L.stream, L.inst, \
+                     L.items, begin, L.xcd, Qin, Qout, RR, a, b, first)
+  constexpr int parts = BatchLine<N, EPB>::PARTS;
   if (L.f32) {
-    if (mode == 0) DG_LD(0, true);
-    else DG_LD(1, true);
+    if (mode == 0) DG_LD(k_batch_degree32, 0, 1, BNT);
+    else DG_LD(k_batch_degree32, 1, 1, BNT);
   } else {
-    if (mode == 0) DG_LD(0, false);
-    else DG_LD(1, false);
+    if (mode == 0) DG_LD(k_batch_degree, 0, parts, 64);
+    else DG_LD(k_batch_degree, 1, parts, 64);
   }
 #undef DG_LD
 }

@@ -18,6 +18,7 @@
 #include "dg_internal.h"
 #include "stage_fp64.h"
 #include "stage_nb.h"
+#include "stage_line.h"
 
 namespace {
 
@@ -75,6 +76,33 @@ k_stage_nb(DGTables tb, const double* __restrict__ Qin, double* __restrict__ Qou
   int e0, ne;
   dgdev::block_elements<EPB>(tb, ord, blockIdx.x, gridDim.x, e0, ne);
   dgdev::stage_nb_body<N, MODE, EPB, NT, kLines<N>>(tb, Qin, Qout, RR, rka, rkb, dt, first, e0, ne, smem, threadIdx.x);
+}
+
+// One thread per line (stage_line.h): elements per wave, as many as have
+// their N^2 lines, and their pairs of y/z neighbour points, in one wave.
+template <int N> struct LineCfg { static constexpr int EPB = N == 2 ? 16 : N == 3 ? 5 : N == 4 ? 4 : N == 5 ? 2 : 1; };
+
+// Launches of up to this many waves (two per CU) go to k_stage_nb: with the
+// chip that empty a stage takes as long as one workgroup, and a wave that
+// holds whole lines runs longer than four that hold a node per thread
+// (us per stage, k_stage_nb against k_stage_line: 8^3 p=3 7.5 / 8.8, 8^3 p=5
+// 12.7 / 13.7, 8^3 p=7 18.0 / 19.4; above, 14^3 p=3 13.1 / 12.5, 10^3 p=5
+// 15.7 / 14.3, 10^3 p=7 30.7 / 26.3).  At N = 3, where the node kernel reads
+// one point per lane, lines are faster at every size (8^3 p=2 8.1 / 7.5).
+constexpr unsigned kLineMinWaves = 512;
+
+// Stage kernel with one thread per line, Qin -> Qout.  At 48^3 p=4 the HBM
+// stream bounds it (stages 2..5: 534 us against 632 with a thread per node;
+// reading and writing its state and residual alone takes 450): taking the
+// flux arithmetic out leaves its time as it is.
+template <int N, int MODE>
+__global__ void __launch_bounds__(64, N == 8 ? 1 : 2)
+k_stage_line(DGTables tb, const double* __restrict__ Qin, double* __restrict__ Qout, double* __restrict__ RR,
+             double rka, double rkb, double dt, int first, DGOrder ord) {
+  constexpr int EPB = LineCfg<N>::EPB;
+  __shared__ __align__(16) double smem[dgdev::LineSmem<N, EPB>::size];
+  const dgdev::Block blk = dgdev::block_of<EPB>(tb, ord, blockIdx.x, gridDim.x);
+  dgdev::stage_line_body<N, MODE, EPB>(tb, Qin, Qout, RR, rka, rkb, dt, first, blk, smem, threadIdx.x);
 }
 
 // ---- reductions -----------------------------------------------------------
@@ -187,15 +215,29 @@ template <int N>
 int launch_stage_nb_n(const dg_ctx* c, const double* Qin, double* Qout, double* RR, int mode, double a, double b,
                       double dt, int first) {
   unsigned grid;
-  const DGOrder ord = dg_order(c, Cfg<N>::EPB, &grid);
-  const dim3 blk(Cfg<N>::NT);
-  if (mode == 0)
-    hipLaunchKernelGGL((k_stage_nb<N, 0>), dim3(grid), blk, 0, c->stream, c->tab, Qin, Qout, RR, a, b, dt, first, ord);
-  else if (first)
-    hipLaunchKernelGGL((k_stage_nb<N, 2>), dim3(grid), blk, 0, c->stream, c->tab, Qin, Qout, RR, a, b, dt, first, ord);
-  else
-    hipLaunchKernelGGL((k_stage_nb<N, 1>), dim3(grid), blk, 0, c->stream, c->tab, Qin, Qout, RR, a, b, dt, first, ord);
-  return (int)hipGetLastError();
+#define DG_LAUNCH(kernel, threads)                                                                            \
+  do {                                                                                                        \
+    if (mode == 0)                                                                                            \
+      hipLaunchKernelGGL((kernel<N, 0>), dim3(grid), dim3(threads), 0, c->stream, c->tab, Qin, Qout, RR, a, b, dt, \
+                         first, ord);                                                                         \
+    else if (first)                                                                                           \
+      hipLaunchKernelGGL((kernel<N, 2>), dim3(grid), dim3(threads), 0, c->stream, c->tab, Qin, Qout, RR, a, b, dt, \
+                         first, ord);                                                                         \
+    else                                                                                                      \
+      hipLaunchKernelGGL((kernel<N, 1>), dim3(grid), dim3(threads), 0, c->stream, c->tab, Qin, Qout, RR, a, b, dt, \
+                         first, ord);                                                                         \
+    return (int)hipGetLastError();                                                                            \
+  } while (0)
+  if constexpr (N >= 2) {
+    const DGOrder ord = dg_order(c, LineCfg<N>::EPB, &grid, true);
+    if (N == 3 || grid > kLineMinWaves) DG_LAUNCH(k_stage_line, 64);
+  }
+  if constexpr (N != 3) {
+    const DGOrder ord = dg_order(c, Cfg<N>::EPB, &grid);
+    DG_LAUNCH(k_stage_nb, Cfg<N>::NT);
+  }
+#undef DG_LAUNCH
+  return (int)hipErrorInvalidValue;
 }
 
 template <int N>

@@ -39,27 +39,62 @@ __host__ __device__ __forceinline__ int xcd_block(int w, int nblk) {
   return x * q + (x < r ? x : r) + i;
 }
 
-// Elements [e0, e0 + ne) of workgroup w of nblk under the visiting order o
-// (see DGOrder): always ne <= EPB consecutive elements of one x-row.  Every
-// value is uniform over the workgroup.
+// Elements [e0, e0 + ne), ne <= EPB, of one x-row: x0 .. x0 + ne - 1 of row
+// (y, z).
+struct Block {
+  int e0, ne, x0, y, z;
+};
+
+// The block of workgroup w of nblk under the visiting order o (see DGOrder),
+// a bijection on [0, nblk).  Every value is uniform over the workgroup.
+// With o.xcd (workgroup w runs on XCD w % 8) every share of the order is
+// split into 8 contiguous parts of equal size, one per XCD; what a multiple
+// of 8 leaves of every whole share follows at the end, then a short last
+// share.
+template <int EPB>
+__host__ __device__ __forceinline__ Block block_of(const DGTables& tb, const DGOrder& o, int w, int nblk) {
+  int s = w;
+  if (o.xcd) {
+    const int even = o.full * o.q * 8;
+    if (w < even) {
+      const int i = w >> 3, sh = dg_quot(i, o.dq);
+      s = sh * o.share + (w & 7) * o.q + (i - sh * o.q);
+    } else {
+      const int left = o.share & 7, v = w - even;
+      if (v < o.full * left) {
+        const int sh = v / left;
+        s = sh * o.share + 8 * o.q + (v - sh * left);
+      } else {
+        s = o.full * o.share + xcd_block(v - o.full * left, nblk - o.full * o.share);
+      }
+    }
+  }
+  const int sl = dg_quot(s, o.dslab);
+  int r = s - sl * o.slab;
+  const int tz = imin(o.tz, tb.nz - sl * o.tz);
+  const bool whole = tz == o.tz;
+  const int pen = tb.ny * tz * o.tx;         // blocks of a full pencil of this slab
+  const int px = whole ? dg_quot(r, o.dpen) : r / pen;
+  r -= px * pen;
+  const int tx = imin(o.tx, o.nxb - px * o.tx);
+  const int y = whole && tx == o.tx ? dg_quot(r, o.drow) : r / (tz * tx);
+  r -= y * (tz * tx);
+  const int zz = tz == 1 ? 0 : tx == o.tx ? dg_quot(r, o.dtx) : r / tx;
+  Block b;
+  b.x0 = (px * o.tx + r - zz * tx) * EPB;
+  b.y = y;
+  b.z = sl * o.tz + zz;
+  b.e0 = (b.z * tb.ny + y) * tb.nx + b.x0;
+  b.ne = imin(EPB, tb.nx - b.x0);
+  return b;
+}
+
 template <int EPB>
 __host__ __device__ __forceinline__ void block_elements(const DGTables& tb, const DGOrder& o, int w, int nblk,
                                                         int& e0, int& ne) {
-  const int s = o.xcd ? xcd_block(w, nblk) : w;
-  const int slab = o.nxb * tb.ny * o.tz;     // blocks of a full z-slab
-  const int pz = s / slab;
-  int r = s - pz * slab;
-  const int tz = imin(o.tz, tb.nz - pz * o.tz);
-  const int pen = tb.ny * tz * o.tx;         // blocks of a full pencil of this slab
-  const int px = r / pen;
-  r -= px * pen;
-  const int tx = imin(o.tx, o.nxb - px * o.tx);
-  const int y = r / (tz * tx);
-  r -= y * (tz * tx);
-  const int zz = r / tx;
-  const int x0 = (px * o.tx + r - zz * tx) * EPB;
-  e0 = ((pz * o.tz + zz) * tb.ny + y) * tb.nx + x0;
-  ne = imin(EPB, tb.nx - x0);
+  const Block b = block_of<EPB>(tb, o, w, nblk);
+  e0 = b.e0;
+  ne = b.ne;
 }
 
 // Shared-memory footprint (doubles) of stage_nb_body: the state of the
