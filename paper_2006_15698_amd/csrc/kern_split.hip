@@ -19,8 +19,13 @@
 //   flux of the standard scheme there.  With the central two-point flux this
 //   is exactly the standard weak form.
 //
-// One workgroup per element (elements visited in the neighbour-read stage's
-// order: pencils, each XCD a contiguous part), one thread per node (the
+// k_split_line (the default): one thread per line of nodes, one wave per block
+// of elements (stage_line.h).  It needs about half of k_split's FP64
+// instructions, which held that kernel: 48^3 p=4 927 -> 596 us a stage, 40^3
+// p=3 320 -> 160, 32^3 p=5 640 -> 361, 24^3 p=6 534 -> 245, 24^3 p=7 560 -> 323.
+//
+// k_split (p = 0 and small launches): one workgroup per element (elements
+// visited in the neighbour-read stage's order), one thread per node (the
 // pairwise fluxes make the volume term O(N^4) per element); the face points
 // of each direction on waves of their own.  The last two terms of B_f depend on
 // the face point only, not on the node along the line: they are formed once
@@ -34,6 +39,7 @@
 #include "dg_internal.h"
 #include "stage_fp64.h"
 #include "stage_nb.h"
+#include "stage_line.h"
 
 namespace {
 
@@ -294,9 +300,25 @@ __device__ __forceinline__ void split_face(const DGTables& tb, const double* __r
   lds_put(Tp[face][pt], so);
 }
 
+// The volume weights W_ia (see split_line), odd under reflection of the line
+// like the tables they are built from: the upper half.
+struct SplitTables {
+  double W[DG_MAXN * DG_MAXN / 2];
+};
+
+SplitTables split_tables(const DGTables& t, int N) {
+  SplitTables s;
+  for (int k = 0; k < N * N / 2; ++k) {
+    const int i = k / N, a = k % N;
+    // Dh[a N + i] = w_i l_a'(xi_i) / w_a
+    s.W[k] = 2.0 * (t.Dh[a * N + i] * t.w[a] / t.w[i]) - t.liftp[i] * t.lp[a] + t.liftm[i] * t.lm[a];
+  }
+  return s;
+}
+
 template <int N, int MODE>
 __global__ void __launch_bounds__(SCfg<N>::NT) __attribute__((amdgpu_waves_per_eu(3, 8)))
-k_split(DGTables tb, const double* __restrict__ Qin, double* __restrict__ Qout, double* __restrict__ RR, double a,
+k_split(DGTables tb, SplitTables st, const double* __restrict__ Qin, double* __restrict__ Qout, double* __restrict__ RR, double a,
         double b, double dt, DGOrder ord) {
   constexpr int N2 = SCfg<N>::N2, N3 = SCfg<N>::N3, WPD = SCfg<N>::WPD;
   // per node / face point six doubles (16-byte aligned: three 16-byte accesses)
@@ -313,10 +335,7 @@ k_split(DGTables tb, const double* __restrict__ Qin, double* __restrict__ Qout, 
   const int64_t fs = (int64_t)tb.E * N3;
   const double* qe = Qin + (int64_t)e * N3;
   if (t < N2) {
-    const int i = t / N, aa = t % N;
-    // Dh[a N + i] = w_i l_a'(xi_i) / w_a
-    const double dia = tb.Dh[aa * N + i] * tb.w[aa] / tb.w[i];   // D_ia = l_a'(xi_i)
-    Wm[i][aa] = 2.0 * dia - tb.liftp[i] * tb.lp[aa] + tb.liftm[i] * tb.lm[aa];
+    Wm[t / N][t % N] = t < N2 / 2 ? st.W[t] : 2 * t + 1 == N2 ? 0.0 : -st.W[N2 - 1 - t];
   }
   // face points: wave w < 3 WPD takes 64 points of direction w / WPD (or,
   // below N = 5, thread t takes point t); the neighbour's trace needs no
@@ -369,19 +388,144 @@ k_split(DGTables tb, const double* __restrict__ Qin, double* __restrict__ Qout, 
   }
 }
 
+// ---- one thread per line (stage_line.h) ------------------------------------
+// Two-point flux of two half-primitive states (as kg_flux, the direction's
+// pressure in one FMA).
+template <int D>
+__device__ __forceinline__ void kg_line(const Prim& a, const Prim& b, double* f) {
+  const double pm = a.p + b.p, ud = a.u[D] + b.u[D];
+  const double mass = (a.r + b.r) * ud;
+  f[0] = mass;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) f[1 + k] = k == D ? fma(mass, ud, pm) : mass * (a.u[k] + b.u[k]);
+  f[4] = fma(pm, ud, mass * (a.e + b.e));
+}
+
+// The split form on a thread's line.  With the whole line in registers each
+// two-point flux is evaluated once and added to both of its nodes: N(N+1)/2
+// of them a line instead of N^2, and the N a face needs serve its G term and
+// the nodes alike.
+template <int N>
+struct SplitLine {
+  static constexpr bool BULK = true;   // rates are handed out at the end
+  dgdev::LineTables<N> tab;
+  const SplitTables& st;
+  __device__ __forceinline__ double w(int i, int a) const {
+    const int k = i * N + a;
+    return k < N * N / 2 ? st.W[k] : -st.W[N * N - 1 - k];
+  }
+  template <int D, class Pre, class Emit>
+  __device__ __forceinline__ void rate(const double (&q)[5][N], const double* tl, const double* tr, const double* nl,
+                                       const double* nr, bool act, Pre&& pre, Emit&& emit) const {
+    const DGTables& tb = tab.tb;
+    double r[5][N];   // minus the rate
+    Prim P[N];
+#pragma unroll
+    for (int m = 0; m < N; ++m) {
+      const double c[5] = {q[0][m], q[1][m], q[2][m], q[3][m], q[4][m]};
+      P[m] = to_prim(c, tb.gm1);
+#pragma unroll
+      for (int f = 0; f < 5; ++f) r[f][m] = 0.0;
+    }
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      double G[5];
+      dgdev::lf_flux_d<D>(s ? tr : nl, s ? nr : tl, tb.gamma, tb.gm1, G);
+      const Prim T = to_prim(s ? tr : tl, tb.gm1);
+#pragma unroll
+      for (int m = 0; m < N; ++m) {
+        double f[5];
+        kg_line<D>(T, P[m], f);
+        const double l = s ? tab.lp(m) : tab.lm(m), c = s ? tab.liftp(m) : -tab.liftm(m);
+#pragma unroll
+        for (int v = 0; v < 5; ++v) {
+          r[v][m] = fma(c, f[v], r[v][m]);
+          G[v] = fma(-l, f[v], G[v]);
+          asm volatile("" : "+v"(G[v]), "+v"(r[v][m]));
+        }
+      }
+#pragma unroll
+      for (int m = 0; m < N; ++m) {
+        const double c = s ? tab.liftp(m) : -tab.liftm(m);
+#pragma unroll
+        for (int v = 0; v < 5; ++v) r[v][m] = fma(c, G[v], r[v][m]);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+#pragma unroll
+      for (int a = i; a < N; ++a) {
+        if (2 * i + 1 == N && a == i) continue;   // W is zero at the centre
+        double f[5];
+        kg_line<D>(P[i], P[a], f);
+        const double wi = w(i, a), wa = w(a, i);
+#pragma unroll
+        for (int v = 0; v < 5; ++v) {
+          r[v][i] = fma(wi, f[v], r[v][i]);
+          if (a != i) r[v][a] = fma(wa, f[v], r[v][a]);
+        }
+        // (one pair at a time: interleaved, their terms do not fit the
+        // registers beside the line and its rate)
+#pragma unroll
+        for (int v = 0; v < 5; ++v) {
+          asm volatile("" : "+v"(r[v][i]));
+          if (a != i) asm volatile("" : "+v"(r[v][a]));
+        }
+      }
+    }
+    pre();
+    if (!act) return;
+#pragma unroll
+    for (int v = 0; v < 5; ++v)
+#pragma unroll
+      for (int m = 0; m < N; ++m) emit(v, m, -r[v][m]);
+  }
+};
+
+template <int N> struct SplitCfg { static constexpr int EPB = N == 2 ? 16 : N == 3 ? 5 : N == 4 ? 4 : N == 5 ? 2 : 1; };
+
+template <int N, int MODE>
+__global__ void __launch_bounds__(64, N == 8 ? 1 : N <= 3 ? 3 : 2)
+k_split_line(DGTables tb, SplitTables st, const double* __restrict__ Qin, double* __restrict__ Qout,
+             double* __restrict__ RR, double a, double b, double dt, DGOrder ord) {
+  constexpr int EPB = SplitCfg<N>::EPB;
+  __shared__ __align__(16) double smem[dgdev::LineSmem<N, EPB>::size];
+  const dgdev::Block blk = dgdev::block_of<EPB>(tb, ord, blockIdx.x, gridDim.x);
+  dgdev::stage_line_body<N, MODE, EPB>(SplitLine<N>{{tb}, st}, tb, Qin, Qout, RR, a, b, dt, 0, blk, smem, threadIdx.x);
+}
+
+// Launches of up to this many waves stay on k_split from N = 4: an element's
+// whole line on one thread then runs longer than its nodes on several waves
+// (8^3 p=4 13.0 against 10.5 us a stage, 8^3 p=3 10.4 / 8.6; above, 12^3 p=3
+// 13.1 / 14.7, 12^3 p=4 17.8 / 19.0, 8^3 p=6 19.5 / 19.9).
+constexpr unsigned kSplitLineMinWaves = 384;
+
 template <int N>
 int launch_split_n(const dg_ctx* c, const double* Qin, double* Qout, double* RR, int mode, double a, double b,
                    double dt) {
   unsigned grid;
-  const DGOrder ord = dg_order(c, 1, &grid);
-  const dim3 blk(SCfg<N>::NT);
-  if (mode == 0)
-    hipLaunchKernelGGL((k_split<N, 0>), dim3(grid), blk, 0, c->stream, c->tab, Qin, Qout, RR, a, b, dt, ord);
-  else if (mode == 2)
-    hipLaunchKernelGGL((k_split<N, 2>), dim3(grid), blk, 0, c->stream, c->tab, Qin, Qout, RR, a, b, dt, ord);
-  else
-    hipLaunchKernelGGL((k_split<N, 1>), dim3(grid), blk, 0, c->stream, c->tab, Qin, Qout, RR, a, b, dt, ord);
-  return (int)hipGetLastError();
+#define DG_LAUNCH(kernel, threads, ...)                                                                            \
+  do {                                                                                                             \
+    const dim3 blk(threads);                                                                                       \
+    if (mode == 0)                                                                                                 \
+      hipLaunchKernelGGL((kernel<N, 0>), dim3(grid), blk, 0, c->stream, c->tab, __VA_ARGS__, Qin, Qout, RR, a, b, dt, ord); \
+    else if (mode == 2)                                                                                            \
+      hipLaunchKernelGGL((kernel<N, 2>), dim3(grid), blk, 0, c->stream, c->tab, __VA_ARGS__, Qin, Qout, RR, a, b, dt, ord); \
+    else                                                                                                           \
+      hipLaunchKernelGGL((kernel<N, 1>), dim3(grid), blk, 0, c->stream, c->tab, __VA_ARGS__, Qin, Qout, RR, a, b, dt, ord); \
+    return (int)hipGetLastError();                                                                                 \
+  } while (0)
+  const SplitTables st = split_tables(c->tab, N);
+  if constexpr (N >= 2) {
+    const DGOrder ord = dg_order(c, SplitCfg<N>::EPB, &grid, true);
+    if (N <= 3 || grid > kSplitLineMinWaves) DG_LAUNCH(k_split_line, 64, st);
+  }
+  if constexpr (N == 1 || N >= 4) {
+    const DGOrder ord = dg_order(c, 1, &grid);
+    DG_LAUNCH(k_split, SCfg<N>::NT, st);
+  }
+#undef DG_LAUNCH
+  return (int)hipErrorInvalidValue;
 }
 
 }  // namespace

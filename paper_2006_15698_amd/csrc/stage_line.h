@@ -105,42 +105,51 @@ __device__ __forceinline__ void store_pair_trace(const double2 (&w)[N], const do
   h[1] = v1;
 }
 
-// Rate of direction D on the thread's line q[field][node]: volume
-// contraction plus the lift of the two Lax-Friedrichs fluxes, handed to
-// `emit(f, m, s)` for every field and node.  tl, tr: the line's own end
-// traces; nl, nr: the - and + neighbour's traces.
-template <int N, int D, class Emit>
-__device__ __forceinline__ void line_rate(const LineTables<N>& t, const double (&q)[5][N], const double* tl,
-                                          const double* tr, const double* nl, const double* nr, Emit&& emit) {
-  double fl[5], fr[5], pr[N], ud[N];
-  lf_flux_d<D>(nl, tl, t.tb.gamma, t.tb.gm1, fl);
-  lf_flux_d<D>(tr, nr, t.tb.gamma, t.tb.gm1, fr);
-#pragma unroll
-  for (int a = 0; a < N; ++a) {
-    const double rinv = recip(q[0][a]);
-    pr[a] = t.tb.gm1 * (q[4][a] - 0.5 * (q[1][a] * q[1][a] + q[2][a] * q[2][a] + q[3][a] * q[3][a]) * rinv);
-    ud[a] = q[1 + D][a] * rinv;
-  }
-#pragma unroll
-  for (int f = 0; f < 5; ++f) {
-    double F[N];
+// The standard form's rate of direction D on the thread's line
+// q[field][node]: volume contraction plus the lift of the two Lax-Friedrichs
+// fluxes, handed to `emit(f, m, s)` for every field and node (2/h_D times s
+// is the rate) of an active lane, after `pre()` on every lane.  tl, tr: the
+// line's own end traces; nl, nr: the - and + neighbour's traces.
+template <int N>
+struct EulerLine {
+  static constexpr bool BULK = false;   // rates are handed out field by field
+  LineTables<N> tab;
+  template <int D, class Pre, class Emit>
+  __device__ __forceinline__ void rate(const double (&q)[5][N], const double* tl, const double* tr, const double* nl,
+                                       const double* nr, bool act, Pre&& pre, Emit&& emit) const {
+    const LineTables<N>& t = tab;
+    pre();
+    if (!act) return;
+    double fl[5], fr[5], pr[N], ud[N];
+    lf_flux_d<D>(nl, tl, t.tb.gamma, t.tb.gm1, fl);
+    lf_flux_d<D>(tr, nr, t.tb.gamma, t.tb.gm1, fr);
 #pragma unroll
     for (int a = 0; a < N; ++a) {
-      if (f == 0) F[a] = q[1 + D][a];
-      else if (f == 4) F[a] = (q[4][a] + pr[a]) * ud[a];
-      else F[a] = q[f][a] * ud[a] + (D == f - 1 ? pr[a] : 0.0);
+      const double rinv = recip(q[0][a]);
+      pr[a] = t.tb.gm1 * (q[4][a] - 0.5 * (q[1][a] * q[1][a] + q[2][a] * q[2][a] + q[3][a] * q[3][a]) * rinv);
+      ud[a] = q[1 + D][a] * rinv;
     }
 #pragma unroll
-    for (int m = 0; m < N; ++m) {
-      double s = 0.0;
+    for (int f = 0; f < 5; ++f) {
+      double F[N];
 #pragma unroll
-      for (int a = 0; a < N; ++a) s = fma(t.dh(m, a), F[a], s);
-      s = fma(t.liftm(m), fl[f], s);
-      s = fma(-t.liftp(m), fr[f], s);
-      emit(f, m, s);
+      for (int a = 0; a < N; ++a) {
+        if (f == 0) F[a] = q[1 + D][a];
+        else if (f == 4) F[a] = (q[4][a] + pr[a]) * ud[a];
+        else F[a] = q[f][a] * ud[a] + (D == f - 1 ? pr[a] : 0.0);
+      }
+#pragma unroll
+      for (int m = 0; m < N; ++m) {
+        double s = 0.0;
+#pragma unroll
+        for (int a = 0; a < N; ++a) s = fma(t.dh(m, a), F[a], s);
+        s = fma(t.liftm(m), fl[f], s);
+        s = fma(-t.liftp(m), fr[f], s);
+        emit(f, m, s);
+      }
     }
   }
-}
+};
 
 // Both end traces of a line (the FMA chain of line_trace).
 template <int N>
@@ -159,10 +168,11 @@ __device__ __forceinline__ void end_traces(const LineTables<N>& t, const double 
   }
 }
 
-// The elements of block blk, 1 <= ne <= EPB, on one wave; the other arguments
-// and MODE as for stage_nb_body.  smem: LineSmem<N, EPB>::size doubles.
-template <int N, int MODE, int EPB>
-__device__ __forceinline__ void stage_line_body(const DGTables& tb, const double* __restrict__ Qin,
+// The elements of block blk, 1 <= ne <= EPB, on one wave, with the rate of the
+// volume form `form` (EulerLine; kern_split.hip has another); the other
+// arguments and MODE as for stage_nb_body.  smem: LineSmem<N, EPB>::size doubles.
+template <int N, int MODE, int EPB, class Form>
+__device__ __forceinline__ void stage_line_body(const Form& form, const DGTables& tb, const double* __restrict__ Qin,
                                                 double* __restrict__ Qout, double* __restrict__ RR, double rka,
                                                 double rkb, double dt, int first, const Block& blk, double* smem,
                                                 int lane) {
@@ -176,6 +186,9 @@ __device__ __forceinline__ void stage_line_body(const DGTables& tb, const double
   double* sS = smem;             // [5][SF] state
   double* sA = smem + 5 * SF;    // [5][SF] rate
   double* sT = sA;               // [2][5][FP] neighbour traces, before the rate is first written
+  // a form that hands out its rates at its end (Form::BULK) leaves the y- and
+  // z-traces in LDS beside each other until then, which frees 40 registers
+  constexpr bool KEEP = Form::BULK && 20 * FP <= 5 * SF;
 
   const int nx = tb.nx, ny = tb.ny, nz = tb.nz;
   const int64_t EN3 = (int64_t)tb.E * N3;
@@ -193,7 +206,7 @@ __device__ __forceinline__ void stage_line_body(const DGTables& tb, const double
   //         the first is waited for; then every consumed field of the x- and
   //         y-lines issues the field of the y- and z-lines that takes its
   //         registers.
-  const LineTables<N> tab{tb};
+  const LineTables<N>& tab = form.tab;
   // own state, node pairs of the contiguous per-field span (past its end the
   // last pair is read, and written, again)
   const int64_t span = (int64_t)e0 * N3;
@@ -267,12 +280,12 @@ __device__ __forceinline__ void stage_line_body(const DGTables& tb, const double
   const int el = ln / N2, pt = ln - el * N2;
   const int b = pt / N, a = pt - b * N;
   double q[5][N], tl[5], tr[5], nl[3][5], nr[3][5];
-  auto take = [&](int d) {
+  auto take = [&](int d, int off = 0) {
     __syncthreads();
 #pragma unroll
     for (int f = 0; f < 5; ++f) {
-      nl[d][f] = sT[f * FP + ln];
-      nr[d][f] = sT[(5 + f) * FP + ln];
+      nl[d][f] = sT[off + f * FP + ln];
+      nr[d][f] = sT[off + (5 + f) * FP + ln];
     }
     __syncthreads();
   };
@@ -338,25 +351,32 @@ __device__ __forceinline__ void stage_line_body(const DGTables& tb, const double
     load_pair_line<N, 2>(zb + f * EN3, w[f]);
     __builtin_amdgcn_sched_barrier(0);
   }
-  take(1);
+  if (!KEEP) take(1);
 #pragma unroll
   for (int f = 0; f < 5; ++f) {
-    if (paired) store_pair_trace<N>(w[f], pc, pT + f * FP);
+    if (paired) store_pair_trace<N>(w[f], pc, pT + (KEEP ? 10 * FP : 0) + f * FP);
   }
-  take(2);
-  if constexpr (EPB == 1) read_x();
+  if (!KEEP) take(2);
+  // (read again where it was not held through the loads above)
+  if constexpr (EPB == 1 || Form::BULK) read_x();
 
   // ---- C: the three directions, summed through sA in the order x, y, z
   {
     double* o = sA + L::row(el, b, a);
     const double sc = tb.sc[0];
-    if (act)
-      line_rate<N, 0>(tab, q, tl, tr, nl[0], nr[0], [&](int f, int m, double s) { o[f * SF + m] = fma(sc, s, 0.0); });
+    form.template rate<0>(
+          q, tl, tr, nl[0], nr[0], act,
+          [&] {
+            if (KEEP) {
+              take(1);
+              take(2, 10 * FP);
+            }
+          },
+          [&](int f, int m, double s) { o[f * SF + m] = fma(sc, s, 0.0); });
   }
   __syncthreads();
   double2 r[UPT][5];
-  if (MODE == 1) {
-    // the residual: its latency overlaps the y- and z-lines
+  auto read_res = [&] {
 #pragma unroll
     for (int u = 0; u < UPT; ++u) {
       const int g = imin(2 * (lane + 64 * u), cnt - 2);
@@ -364,7 +384,10 @@ __device__ __forceinline__ void stage_line_body(const DGTables& tb, const double
       for (int f = 0; f < 5; ++f) r[u][f] = load_pair_nt(RR + f * EN3 + span + g);
     }
     __builtin_amdgcn_sched_barrier(0);
-  }
+  };
+  // the residual: its latency overlaps the y- and z-lines where their rates
+  // leave its registers free
+  if (MODE == 1 && !Form::BULK) read_res();
   {
     int o[N];   // y-line: i = a, k = b
 #pragma unroll
@@ -375,8 +398,7 @@ __device__ __forceinline__ void stage_line_body(const DGTables& tb, const double
       for (int m = 0; m < N; ++m) q[f][m] = sS[f * SF + o[m]];
     end_traces<N>(tab, q, tl, tr);
     const double sc = tb.sc[1];
-    if (act)
-      line_rate<N, 1>(tab, q, tl, tr, nl[1], nr[1], [&](int f, int m, double s) {
+    form.template rate<1>(q, tl, tr, nl[1], nr[1], act, [] {}, [&](int f, int m, double s) {
         sA[f * SF + o[m]] = fma(sc, s, sA[f * SF + o[m]]);
       });
   }
@@ -391,11 +413,11 @@ __device__ __forceinline__ void stage_line_body(const DGTables& tb, const double
       for (int m = 0; m < N; ++m) q[f][m] = sS[f * SF + o[m]];
     end_traces<N>(tab, q, tl, tr);
     const double sc = tb.sc[2];
-    if (act)
-      line_rate<N, 2>(tab, q, tl, tr, nl[2], nr[2], [&](int f, int m, double s) {
+    form.template rate<2>(q, tl, tr, nl[2], nr[2], act, [] {}, [&](int f, int m, double s) {
         sA[f * SF + o[m]] = fma(sc, s, sA[f * SF + o[m]]);
       });
   }
+  if (MODE == 1 && Form::BULK) read_res();
   __syncthreads();
 
   // ---- D: output, node pairs of the per-field spans

@@ -53,3 +53,32 @@ def test_line_kernel_bitwise_equals_node_kernel(dgm, p, n):
     for o in outs[1:]:
         for a, b in zip(outs[0], o):
             assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("p,n", [(1, (33, 5, 4)), (2, (7, 5, 4)), (3, (5, 13, 21)), (4, (3, 13, 21)), (5, (3, 13, 21)),
+                                 (6, (1, 25, 21)), (7, (2, 13, 21))])
+def test_split_line_kernel_vs_oracle(dgm, p, n):
+    """The split form's line kernel (meshes of more than 384 waves) on
+    elements at the row ends and corners and seeded ones, each against the
+    oracle on the 3x3x3 periodic patch around it, summand-scaled 1e-12."""
+    import numpy as np
+    import torch
+    from oracle.splitform import SplitFormDG
+    from tests.parity import TOL, patch_rhs, split_summand_scale
+    L = (1.0, 0.8, 1.3)
+    print(f"[split line kernel p={p} n={n}]", flush=True)
+    Q = W.random_smooth(n, p, seed=70 + p, L=L, noise=0.02)
+    s = dgm.Solver(n, p, L=L, volume_form=dgm.DG_VOLUME_KEP)
+    R = s.rhs(torch.from_numpy(Q).cuda()).cpu().numpy()
+    nx, ny, nz = n
+    rng = np.random.default_rng(p)
+    elems = {(0, 0, 0), (nx - 1, ny - 1, nz - 1), (nx - 1, 0, 1), (0, ny - 1, nz - 2)}
+    elems |= {tuple(int(rng.integers(0, m)) for m in n) for _ in range(4)}
+    ref = patch_rhs(n, p, L, Q, sorted(elems), make=SplitFormDG)
+    small = SplitFormDG((3, 3, 3), p, L=tuple(3 * np.array(L) / np.array(n)))
+    for (ex, ey, ez), Ro in ref.items():
+        patch = np.ascontiguousarray(Q[:, [(ez + o) % nz for o in (-1, 0, 1)]][:, :, [(ey + o) % ny for o in (-1, 0, 1)]]
+                                     [:, :, :, [(ex + o) % nx for o in (-1, 0, 1)]])
+        scale = split_summand_scale(small, patch) + np.abs(Ro).reshape(5, -1).max(axis=1)
+        err = np.abs(R[:, ez, ey, ex] - Ro).reshape(5, -1).max(axis=1) / scale
+        assert np.all(err <= TOL), ((ex, ey, ez), err)
