@@ -65,13 +65,14 @@ WORKLOADS = {
 
 # Viscous workloads: (dynamic viscosity, Prandtl number).
 VISCOUS = {"tgv48_p4_re1600": (1.0 / 1600.0, 0.71)}
-# Bytes per node and stage of the viscous decomposition (FP64, 5 fields, 12
-# viscous-flux values).  Fused (default): k_visc_flux forms the inviscid rate
-# too (read Q, write the flux and R) 176; k_visc_apply (read the flux, R, Q,
-# res; write Q, res) 296.  Separate: the inviscid rate (read Q, write R) 80,
-# k_visc_flux (read Q, write the flux) 136, k_visc_apply 296.
-VISC_BYTES = {"rhs": 80, "visc": 136 + 296}
-VISC_BYTES_FUSED = {"visc": 176 + 296}
+# Bytes per node and stage of the viscous decomposition (FP64, 5 fields, four
+# viscous-flux values per face point: 24 N^2 per element, 192 / N bytes a
+# node, N = 5).  Fused (default): k_visc_line forms the inviscid rate too
+# (read Q, write R and the face traces), k_visc_update (read the traces, R, Q,
+# res; write Q, res).  Separate: the inviscid rate (read Q, write R) 80, and
+# k_visc_line reads R too.
+VISC_BYTES = {"rhs": 80, "visc": 120 + 200 + 2 * 192 / 5}
+VISC_BYTES_FUSED = {"visc": 80 + 200 + 2 * 192 / 5}
 # Workloads on the split-form volume term (DG_VOLUME_KEP).
 SPLIT_FORM = {"tgv48_p4_kep"}
 
@@ -90,7 +91,8 @@ def flops_per_dof_stage(N):
 # tables and launch parameters), the batched kernels and the
 # neighbour-read adjoint kernel.
 _COMMON_SOURCES = ["paper_2006_15698_amd/csrc/dg_internal.h",
-                   "paper_2006_15698_amd/csrc/stage_fp64.h", "paper_2006_15698_amd/csrc/stage_nb.h"]
+                   "paper_2006_15698_amd/csrc/stage_fp64.h", "paper_2006_15698_amd/csrc/stage_nb.h",
+                   "paper_2006_15698_amd/csrc/stage_line.h"]
 _FP32_SOURCES = ["paper_2006_15698_amd/csrc/stage_fp32.h", "paper_2006_15698_amd/csrc/stage_nb32.h"]
 STAGE_SOURCES = {
     "fp64": _COMMON_SOURCES + ["paper_2006_15698_amd/csrc/kern_fp64.hip"],
@@ -99,7 +101,8 @@ STAGE_SOURCES = {
                                                 "paper_2006_15698_amd/csrc/kern_batch.hip",
                                                 "paper_2006_15698_amd/csrc/batch_api.cpp"],
     "vjp": _COMMON_SOURCES + ["paper_2006_15698_amd/csrc/kern_vjp.hip"],
-    "visc": _COMMON_SOURCES + ["paper_2006_15698_amd/csrc/kern_visc.hip"],
+    "visc": _COMMON_SOURCES + ["paper_2006_15698_amd/csrc/kern_visc.hip",
+                               "paper_2006_15698_amd/csrc/kern_visc_line.hip"],
     "split": _COMMON_SOURCES + ["paper_2006_15698_amd/csrc/kern_split.hip"],
     "varp": _COMMON_SOURCES + ["paper_2006_15698_amd/csrc/dg_varp.h", "paper_2006_15698_amd/csrc/kern_varp.hip",
                                "paper_2006_15698_amd/csrc/kern_varp_hang.hip",
@@ -848,9 +851,9 @@ def main():
         dg.dg_set_timing(s.ctx, False)
         fused = t["rhs"][1] == 0
         vb = VISC_BYTES_FUSED if fused else VISC_BYTES
-        labels = {"rhs": "inviscid rate (k_stage_nb, RHS mode)",
-                  "visc": ("k_visc_flux (with the inviscid rate) + k_visc_apply" if fused
-                           else "k_visc_flux + k_visc_apply")}
+        labels = {"rhs": "inviscid rate (k_stage_line, RHS mode)",
+                  "visc": ("k_visc_line (with the inviscid rate) + k_visc_update" if fused
+                           else "k_visc_line + k_visc_update")}
         parts = {}
         for kind in vb:
             k_ms, k_n = t[kind]
@@ -862,9 +865,9 @@ def main():
         out["roofline"] = {"bound": "hbm", "achieved": v["achieved"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
                            "frac": v["achieved"] / HBM_PEAK_GBS,
                            "traffic": measured_traffic(args.workload, "visc", s.options()),
-                           "kernel": (("k_visc_flux (viscous flux and inviscid rate) + k_visc_apply (viscous "
+                           "kernel": (("k_visc_line (inviscid rate and own viscous part) + k_visc_update (viscous "
                                        "rate and LSERK45 update), one stage") if fused else
-                                      "k_visc_flux + k_visc_apply (viscous terms and LSERK45 update, one stage)"),
+                                      "k_visc_line + k_visc_update (viscous terms and LSERK45 update, one stage)"),
                            "avg_launch_us": v["avg_launch_us"], "launches": v["launches"],
                            "alg_bytes_per_launch": v["alg_bytes_per_launch"],
                            "stage_bytes_per_node": sum(vb.values())}
@@ -887,10 +890,10 @@ def main():
         f_ms, f_n = t["stage_first"]
         f_s = f_ms / f_n * 1e-3
         traffic = measured_traffic(args.workload, args.precision, s.options())
-        kname = {("neighbour", "fp64"): "k_stage_nb", ("neighbour", "fp32"): "k_stage_nb32",
+        kname = {("neighbour", "fp64"): "k_stage_line", ("neighbour", "fp32"): "k_stage_nb32",
                  ("traces", "fp64"): "k_stage", ("traces", "fp32"): "k_stage32"}[(args.exchange, args.precision)]
         if split:
-            kname = "k_split (split-form volume term, Kennedy-Gruber two-point flux)"
+            kname = "k_split_line (split-form volume term, Kennedy-Gruber two-point flux)"
             traffic = measured_traffic(args.workload, "split", s.options())
         out["roofline"] = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                            "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,

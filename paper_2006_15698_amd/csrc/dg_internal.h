@@ -156,7 +156,7 @@ struct DGWorkspace {
   size_t off_vjp;       // adjoint scratch: two state-sized buffers
   size_t off_q2;        // second state buffer of the neighbour-read path
   size_t off_visc_r;    // viscous terms only (mu > 0): the inviscid rate of a stage (5 N^3 E doubles)
-  size_t off_visc_fv;   //   and the nodal viscous flux (12 N^3 E doubles)
+  size_t off_visc_fv;   //   and the nodal viscous flux (12 N^3 E doubles) or its face traces (24 N^2 E)
   size_t total;
 };
 DGWorkspace dg_workspace_layout(const dg_ctx* c);

@@ -476,9 +476,11 @@ struct SplitLine {
     pre();
     if (!act) return;
 #pragma unroll
-    for (int v = 0; v < 5; ++v)
+    for (int v = 0; v < 5; ++v) {
 #pragma unroll
-      for (int m = 0; m < N; ++m) emit(v, m, -r[v][m]);
+      for (int m = 0; m < N; ++m) r[v][m] = -r[v][m];
+      emit(v, r[v]);
+    }
   }
 };
 

@@ -105,10 +105,22 @@ __device__ __forceinline__ void store_pair_trace(const double2 (&w)[N], const do
   h[1] = v1;
 }
 
+// x[o[m]] = fma(c, v[m], x[o[m]]) along a line in LDS (or = fma(c, v[m], 0)):
+// all reads before the first write, which the compiler, not knowing the
+// places distinct, would have to wait for one by one.
+template <int N>
+__device__ __forceinline__ void add_line(double* x, const int (&o)[N], double c, const double (&v)[N], bool first) {
+  double r[N];
+#pragma unroll
+  for (int m = 0; m < N; ++m) r[m] = first ? 0.0 : x[o[m]];
+#pragma unroll
+  for (int m = 0; m < N; ++m) x[o[m]] = fma(c, v[m], r[m]);
+}
+
 // The standard form's rate of direction D on the thread's line
 // q[field][node]: volume contraction plus the lift of the two Lax-Friedrichs
-// fluxes, handed to `emit(f, m, s)` for every field and node (2/h_D times s
-// is the rate) of an active lane, after `pre()` on every lane.  tl, tr: the
+// fluxes, handed to `emit(f, s)` for every field (2/h_D times s[node] is the
+// rate) of an active lane, after `pre()` on every lane.  tl, tr: the
 // line's own end traces; nl, nr: the - and + neighbour's traces.
 template <int N>
 struct EulerLine {
@@ -131,7 +143,7 @@ struct EulerLine {
     }
 #pragma unroll
     for (int f = 0; f < 5; ++f) {
-      double F[N];
+      double F[N], s[N];
 #pragma unroll
       for (int a = 0; a < N; ++a) {
         if (f == 0) F[a] = q[1 + D][a];
@@ -140,13 +152,13 @@ struct EulerLine {
       }
 #pragma unroll
       for (int m = 0; m < N; ++m) {
-        double s = 0.0;
+        double v = 0.0;
 #pragma unroll
-        for (int a = 0; a < N; ++a) s = fma(t.dh(m, a), F[a], s);
-        s = fma(t.liftm(m), fl[f], s);
-        s = fma(-t.liftp(m), fr[f], s);
-        emit(f, m, s);
+        for (int a = 0; a < N; ++a) v = fma(t.dh(m, a), F[a], v);
+        v = fma(t.liftm(m), fl[f], v);
+        s[m] = fma(-t.liftp(m), fr[f], v);
       }
+      emit(f, s);
     }
   }
 };
@@ -362,7 +374,9 @@ __device__ __forceinline__ void stage_line_body(const Form& form, const DGTables
 
   // ---- C: the three directions, summed through sA in the order x, y, z
   {
-    double* o = sA + L::row(el, b, a);
+    int o[N];
+#pragma unroll
+    for (int m = 0; m < N; ++m) o[m] = L::row(el, b, a) + m;
     const double sc = tb.sc[0];
     form.template rate<0>(
           q, tl, tr, nl[0], nr[0], act,
@@ -372,7 +386,7 @@ __device__ __forceinline__ void stage_line_body(const Form& form, const DGTables
               take(2, 10 * FP);
             }
           },
-          [&](int f, int m, double s) { o[f * SF + m] = fma(sc, s, 0.0); });
+          [&](int f, const double(&s)[N]) { add_line<N>(sA + f * SF, o, sc, s, true); });
   }
   __syncthreads();
   double2 r[UPT][5];
@@ -398,8 +412,8 @@ __device__ __forceinline__ void stage_line_body(const Form& form, const DGTables
       for (int m = 0; m < N; ++m) q[f][m] = sS[f * SF + o[m]];
     end_traces<N>(tab, q, tl, tr);
     const double sc = tb.sc[1];
-    form.template rate<1>(q, tl, tr, nl[1], nr[1], act, [] {}, [&](int f, int m, double s) {
-        sA[f * SF + o[m]] = fma(sc, s, sA[f * SF + o[m]]);
+    form.template rate<1>(q, tl, tr, nl[1], nr[1], act, [] {}, [&](int f, const double(&s)[N]) {
+        add_line<N>(sA + f * SF, o, sc, s, false);
       });
   }
   __syncthreads();
@@ -413,8 +427,8 @@ __device__ __forceinline__ void stage_line_body(const Form& form, const DGTables
       for (int m = 0; m < N; ++m) q[f][m] = sS[f * SF + o[m]];
     end_traces<N>(tab, q, tl, tr);
     const double sc = tb.sc[2];
-    form.template rate<2>(q, tl, tr, nl[2], nr[2], act, [] {}, [&](int f, int m, double s) {
-        sA[f * SF + o[m]] = fma(sc, s, sA[f * SF + o[m]]);
+    form.template rate<2>(q, tl, tr, nl[2], nr[2], act, [] {}, [&](int f, const double(&s)[N]) {
+        add_line<N>(sA + f * SF, o, sc, s, false);
       });
   }
   if (MODE == 1 && Form::BULK) read_res();

@@ -82,3 +82,42 @@ def test_split_line_kernel_vs_oracle(dgm, p, n):
         scale = split_summand_scale(small, patch) + np.abs(Ro).reshape(5, -1).max(axis=1)
         err = np.abs(R[:, ez, ey, ex] - Ro).reshape(5, -1).max(axis=1) / scale
         assert np.all(err <= TOL), ((ex, ey, ez), err)
+
+
+@pytest.mark.parametrize("p,n", [(1, (33, 5, 4)), (2, (7, 5, 4)), (3, (5, 13, 21)), (4, (3, 13, 21)), (5, (6, 28, 25)),
+                                 (6, (2, 13, 21)), (7, (5, 21, 20))])
+def test_viscous_line_kernels(dgm, p, n):
+    """The viscous line kernels (meshes above their smallest size) on elements
+    at the row ends and corners, each against the oracle on the 5x5x5 periodic
+    patch around it, summand-scaled 1e-12; and bitwise the same with the
+    inviscid rate from a launch of its own."""
+    import numpy as np
+    import torch
+    from oracle.viscous import NavierStokesDG
+    from tests.parity import TOL, patch_rhs_viscous, summand_scale, visc_summand_scale
+    L, mu, pr = (1.0, 0.8, 1.3), 0.01, 0.71
+    print(f"[viscous line kernels p={p} n={n}]", flush=True)
+    Q = W.random_smooth(n, p, seed=80 + p, L=L, noise=0.01)
+    Qd = torch.from_numpy(Q).cuda()
+    outs = []
+    for fused in (1, 0):
+        s = dgm.Solver(n, p, L=L, mu=mu, prandtl=pr)
+        s.set_option(dgm.DG_OPT_VISC_FUSED, fused)
+        Qs, res = Qd.clone(), torch.ones_like(Qd)
+        R = s.rhs(Qd)
+        s.step(Qs, res, 1e-6, nsteps=2)
+        torch.cuda.synchronize()
+        outs.append((R, Qs, res))
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
+    R = outs[0][0].cpu().numpy()
+    nx, ny, nz = n
+    elems = [(0, 0, 0), (nx - 1, ny - 1, nz - 1), (nx // 2, 0, nz - 2)]
+    ref = patch_rhs_viscous(n, p, L, Q, elems, mu, pr)
+    small = NavierStokesDG((5, 5, 5), p, L=tuple(5 * np.array(L) / np.array(n)), mu=mu, prandtl=pr)
+    for (ex, ey, ez), Ro in ref.items():
+        xs, ys, zs = ([(e + o) % m for o in range(-2, 3)] for e, m in zip((ex, ey, ez), n))
+        patch = np.ascontiguousarray(Q[:, zs][:, :, ys][:, :, :, xs])
+        scale = summand_scale(small, patch) + visc_summand_scale(small, patch) + np.abs(Ro).reshape(5, -1).max(axis=1)
+        err = np.abs(R[:, ez, ey, ex] - Ro).reshape(5, -1).max(axis=1) / scale
+        assert np.all(err <= TOL), ((ex, ey, ez), err)
