@@ -904,6 +904,11 @@ int dg_rk_stage_vjp(dg_ctx* c, int s, const double* Qs, double* gQ, double* gres
   const int64_t n = (int64_t)(sb / sizeof(double));
   int err = timed(c, TK_VJP, [&] { return dg_launch_axpy(c, n, gres, kRKB[s], gQ, gtot); });
   if (err) return hip_fail(err, "axpy launch");
+  if (c->exchange == DG_EXCHANGE_NEIGHBOUR) {
+    err = timed(c, TK_VJP, [&] { return dg_launch_vjp_stage(c, Qs, gtot, gQ, gres, kRKA[s], dt); });
+    if (err) return hip_fail(err, "reverse stage launch");
+    return DG_OK;
+  }
   err = timed(c, TK_VJP, [&] { return dg_launch_vjp(c, Qs, gtot, v, c->ws); });
   if (err) return hip_fail(err, "vjp launch");
   err = timed(c, TK_VJP, [&] { return dg_launch_rk_reverse(c, n, v, dt, kRKA[s], gtot, gQ, gres); });

@@ -185,6 +185,11 @@ int dg_launch_reduce(const dg_ctx* c, const double* Q, double* red);
 // Adjoint RHS.
 int dg_launch_vjp(const dg_ctx* c, const double* Q, const double* gR, double* gQ, char* scratch);
 
+// Reverse RK stage with neighbour reads: gQ += dt (dR/dQ)^T g in place and
+// gres = a g.
+int dg_launch_vjp_stage(const dg_ctx* c, const double* Q, const double* g, double* gQ, double* gres, double a,
+                        double dt);
+
 // Viscous terms (kern_visc.hip): the nodal viscous flux of Q into Fv (with
 // `rate` also the inviscid rate of the standard form into R), then mode 0:
 // R += the viscous rate; mode 1: the LSERK45 stage in place on Qu and res

@@ -22,8 +22,12 @@
 
 #include "dg_internal.h"
 #include "stage_nb.h"
+#include "vjp_dev.h"
 
 namespace {
+
+using dgdev::flux_vjp;
+using dgdev::lf_vjp_d;
 
 template <int N> struct VCfg;
 template <> struct VCfg<1> { static constexpr int EPB = 64; static constexpr int NT = 64; };
@@ -61,81 +65,6 @@ __device__ __forceinline__ int vneighbour(const DGTables& tb, int e, int d, int 
   int z = ez + dir;
   z = z < 0 ? nz - 1 : (z >= nz ? 0 : z);
   return e + (z - ez) * nx * ny;
-}
-
-// out += (dF^d/dQ)^T g at state q (Eq. (2) with the pressure of Eq. (3)).
-template <int d>
-__device__ __forceinline__ void flux_vjp(const double* q, const double* g, double gm1, double* out) {
-  const double r = dgdev::recip(q[0]);
-  const double u0 = q[1] * r, u1 = q[2] * r, u2 = q[3] * r;
-  const double ud = d == 0 ? u0 : (d == 1 ? u1 : u2);
-  const double pr = gm1 * (q[4] - 0.5 * (q[1] * u0 + q[2] * u1 + q[3] * u2));
-  const double gd = d == 0 ? g[1] : (d == 1 ? g[2] : g[3]);
-  // S = g0 m_d + sum_k g_k m_k u_d + g_d p + g4 (E + p) u_d
-  const double B = g[1] * q[1] + g[2] * q[2] + g[3] * q[3] + g[4] * (q[4] + pr);  // dS/du_d
-  const double P = gd + g[4] * ud;                                                // dS/dp
-  const double usq = u0 * u0 + u1 * u1 + u2 * u2;
-  out[0] += -B * ud * r + P * gm1 * 0.5 * usq;
-  out[1] += g[1] * ud - P * gm1 * u0 + (d == 0 ? g[0] + B * r : 0.0);
-  out[2] += g[2] * ud - P * gm1 * u1 + (d == 1 ? g[0] + B * r : 0.0);
-  out[3] += g[3] * ud - P * gm1 * u2 + (d == 2 ? g[0] + B * r : 0.0);
-  out[4] += g[4] * ud + P * gm1;
-}
-
-// Local wave speed l = |u_d| + c and its gradient dl/dq.
-template <int d>
-__device__ __forceinline__ double wave_speed_grad(const double* q, double gamma, double gm1, double* dl) {
-  const double r = dgdev::recip(q[0]);
-  const double u0 = q[1] * r, u1 = q[2] * r, u2 = q[3] * r;
-  const double ud = d == 0 ? u0 : (d == 1 ? u1 : u2);
-  const double usq = u0 * u0 + u1 * u1 + u2 * u2;
-  const double e = gm1 * (q[4] * r - 0.5 * usq);  // p / rho
-  const double c = dgdev::root(gamma * e);
-  const double sg = ud >= 0.0 ? 1.0 : -1.0;
-  const double k = gamma * dgdev::recip(2.0 * c);
-  // de/drho = gm1 (-E/rho + |u|^2)/rho, de/dm_k = -gm1 u_k / rho, de/dE = gm1 / rho
-  dl[0] = sg * (-ud * r) + k * gm1 * (-q[4] * r + usq) * r;
-  dl[1] = (d == 0 ? sg * r : 0.0) - k * gm1 * u0 * r;
-  dl[2] = (d == 1 ? sg * r : 0.0) - k * gm1 * u1 * r;
-  dl[3] = (d == 2 ? sg * r : 0.0) - k * gm1 * u2 * r;
-  dl[4] = k * gm1 * r;
-  return fabs(ud) + c;
-}
-
-// Transpose of the local Lax-Friedrichs Jacobian for one side, applied to g:
-// minus side:  (1/2) A(qm)^T g + (lambda/2) g - (1/2)(g . (qp - qm)) dlambda/dqm
-// plus side:   (1/2) A(qp)^T g - (lambda/2) g - (1/2)(g . (qp - qm)) dlambda/dqp
-template <int d>
-__device__ __forceinline__ void lf_vjp_d(const double* qm, const double* qp, double gamma, double gm1,
-                                         const double* g, bool minus_side, double* out) {
-  double dlm[5], dlp[5];
-  const double lm = wave_speed_grad<d>(qm, gamma, gm1, dlm);
-  const double lp = wave_speed_grad<d>(qp, gamma, gm1, dlp);
-  const bool pick_m = lm >= lp;
-  const double lam = pick_m ? lm : lp;
-  double gdel = 0.0;
-#pragma unroll
-  for (int f = 0; f < 5; ++f) gdel += g[f] * (qp[f] - qm[f]);
-  double hg[5];
-#pragma unroll
-  for (int f = 0; f < 5; ++f) {
-    hg[f] = 0.5 * g[f];
-    out[f] = 0.0;
-  }
-  double qs[5], dl[5];
-#pragma unroll
-  for (int f = 0; f < 5; ++f) {
-    qs[f] = minus_side ? qm[f] : qp[f];
-    dl[f] = minus_side ? dlm[f] : dlp[f];
-  }
-  flux_vjp<d>(qs, hg, gm1, out);
-  const bool own_selected = minus_side ? pick_m : !pick_m;
-  const double sl = minus_side ? 0.5 * lam : -0.5 * lam;
-#pragma unroll
-  for (int f = 0; f < 5; ++f) {
-    out[f] += sl * g[f];
-    if (own_selected) out[f] -= 0.5 * gdel * dl[f];
-  }
 }
 
 __device__ __forceinline__ void lf_vjp(const double* qm, const double* qp, int d, double gamma, double gm1,
@@ -414,10 +343,14 @@ __device__ __forceinline__ void face_vjp(const double* sQ, const double* sG, int
   lf_vjp_d<D>(qm, qp, gamma, gm1, gf, SIDE != 0, gq);
 }
 
-template <int N>
+// gQ = (dR/dQ)^T gR, or with STAGE the reverse LSERK45 stage around it, where
+// gR is the stage's g: gQ += dt (dR/dQ)^T gR in place and gres = rka gR (no
+// workgroup reads another element's gQ or gres), which saves writing and
+// reading the product (120 bytes a node) and a launch.
+template <int N, bool STAGE>
 __global__ void __launch_bounds__(VCfg<N>::NT)
 k_vjp_nb(DGTables tb, const double* __restrict__ Q, const double* __restrict__ gR, double* __restrict__ gQ,
-         DGOrder ord) {
+         double* __restrict__ gres, double rka, double dt, DGOrder ord) {
   constexpr int EPB = VCfg<N>::EPB, NT = VCfg<N>::NT;
   constexpr int N2 = N * N, N3 = N2 * N, NODES = EPB * N3, FP = EPB * N2, NH = (EPB + 2) * N3;
   constexpr int NW = NT / 64;
@@ -627,7 +560,14 @@ k_vjp_nb(DGTables tb, const double* __restrict__ Q, const double* __restrict__ g
   }
   if (act) {
 #pragma unroll
-    for (int f = 0; f < 5; ++f) gQ[f * EN3 + gofs] = acc[f];
+    for (int f = 0; f < 5; ++f) {
+      if (STAGE) {
+        gQ[f * EN3 + gofs] = fma(dt, acc[f], gQ[f * EN3 + gofs]);
+        gres[f * EN3 + gofs] = rka * g[f];
+      } else {
+        gQ[f * EN3 + gofs] = acc[f];
+      }
+    }
   }
 }
 
@@ -691,29 +631,51 @@ int launch_vjp_n(const dg_ctx* c, const double* Q, const double* gR, double* gQ,
 }
 
 template <int N>
-int launch_vjp_nb_n(const dg_ctx* c, const double* Q, const double* gR, double* gQ) {
+int launch_vjp_nb_n(const dg_ctx* c, const double* Q, const double* gR, double* gQ, double* gres, double a, double dt) {
   unsigned grid;
   const DGOrder ord = dg_order(c, VCfg<N>::EPB, &grid);
-  hipLaunchKernelGGL(k_vjp_nb<N>, dim3(grid), dim3(VCfg<N>::NT), 0, c->stream, c->tab, Q, gR, gQ, ord);
+  const dim3 blk(VCfg<N>::NT);
+  if (gres)
+    hipLaunchKernelGGL((k_vjp_nb<N, true>), dim3(grid), blk, 0, c->stream, c->tab, Q, gR, gQ, gres, a, dt, ord);
+  else
+    hipLaunchKernelGGL((k_vjp_nb<N, false>), dim3(grid), blk, 0, c->stream, c->tab, Q, gR, gQ, gres, a, dt, ord);
   return (int)hipGetLastError();
 }
 
 }  // namespace
 
-int dg_launch_vjp(const dg_ctx* c, const double* Q, const double* gR, double* gQ, char* ws) {
-  if (c->exchange == DG_EXCHANGE_NEIGHBOUR) {
-    switch (c->N) {
-      case 1: return launch_vjp_nb_n<1>(c, Q, gR, gQ);
-      case 2: return launch_vjp_nb_n<2>(c, Q, gR, gQ);
-      case 3: return launch_vjp_nb_n<3>(c, Q, gR, gQ);
-      case 4: return launch_vjp_nb_n<4>(c, Q, gR, gQ);
-      case 5: return launch_vjp_nb_n<5>(c, Q, gR, gQ);
-      case 6: return launch_vjp_nb_n<6>(c, Q, gR, gQ);
-      case 7: return launch_vjp_nb_n<7>(c, Q, gR, gQ);
-      case 8: return launch_vjp_nb_n<8>(c, Q, gR, gQ);
-      default: return (int)hipErrorInvalidValue;
-    }
+// One thread per line (kern_vjp_line.hip), N = 7 and 8; with gres the reverse
+// stage.  There the node kernel's LDS (95 and 139 KB an element) leaves one
+// workgroup on a CU (24^3 p=6 581 against 341 us, 24^3 p=7 1781 / 779); below
+// N = 7 it is the faster one (32^3 p=3 104 / 111, 48^3 p=4 801 / 867, 32^3 p=5
+// 583 / 657): the transposed Lax-Friedrichs Jacobians hold both, and it too
+// forms them one face point a thread.
+int dg_launch_vjp_line(const dg_ctx* c, const double* Q, const double* g, double* G, double* gres, double a,
+                       double dt);
+
+// Neighbour reads: the product into gQ, or with gres the reverse stage.
+static int launch_vjp_neighbour(const dg_ctx* c, const double* Q, const double* gR, double* gQ, double* gres, double a,
+                                double dt) {
+  switch (c->N) {
+    case 1: return launch_vjp_nb_n<1>(c, Q, gR, gQ, gres, a, dt);
+    case 2: return launch_vjp_nb_n<2>(c, Q, gR, gQ, gres, a, dt);
+    case 3: return launch_vjp_nb_n<3>(c, Q, gR, gQ, gres, a, dt);
+    case 4: return launch_vjp_nb_n<4>(c, Q, gR, gQ, gres, a, dt);
+    case 5: return launch_vjp_nb_n<5>(c, Q, gR, gQ, gres, a, dt);
+    case 6: return launch_vjp_nb_n<6>(c, Q, gR, gQ, gres, a, dt);
+    case 7:
+    case 8: return dg_launch_vjp_line(c, Q, gR, gQ, gres, a, dt);
+    default: return (int)hipErrorInvalidValue;
   }
+}
+
+int dg_launch_vjp_stage(const dg_ctx* c, const double* Q, const double* g, double* gQ, double* gres, double a,
+                        double dt) {
+  return launch_vjp_neighbour(c, Q, g, gQ, gres, a, dt);
+}
+
+int dg_launch_vjp(const dg_ctx* c, const double* Q, const double* gR, double* gQ, char* ws) {
+  if (c->exchange == DG_EXCHANGE_NEIGHBOUR) return launch_vjp_neighbour(c, Q, gR, gQ, nullptr, 0.0, 0.0);
   const DGWorkspace L = dg_workspace_layout(c);
   double* TQ = (double*)(ws + L.off_trace0);
   double* TG = (double*)(ws + L.off_trace1);

@@ -121,3 +121,29 @@ def test_viscous_line_kernels(dgm, p, n):
         scale = summand_scale(small, patch) + visc_summand_scale(small, patch) + np.abs(Ro).reshape(5, -1).max(axis=1)
         err = np.abs(R[:, ez, ey, ex] - Ro).reshape(5, -1).max(axis=1) / scale
         assert np.all(err <= TOL), ((ex, ey, ez), err)
+
+
+@pytest.mark.parametrize("p,n", [(1, (5, 3, 4)), (2, (7, 2, 3)), (3, (5, 3, 4)), (4, (3, 5, 2)), (5, (3, 2, 4)),
+                                 (6, (3, 2, 4)), (6, (1, 1, 1)), (7, (2, 3, 3))])
+def test_reverse_stage_bitwise(dgm, p, n):
+    """The reverse stage folded into the adjoint launch (neighbour reads; the
+    line kernel at p = 6, 7) against the trace-buffer sequence of separate
+    launches, for every stage; and the product alone."""
+    import torch
+    print(f"[reverse stage p={p} n={n}]", flush=True)
+    Q = torch.from_numpy(W.random_smooth(n, p, seed=90 + p, noise=0.02)).cuda()
+    gen = torch.Generator().manual_seed(p)
+    g0, r0 = (torch.randn(Q.shape, dtype=torch.float64, generator=gen).cuda() for _ in range(2))
+    outs = []
+    for exchange in (dgm.DG_EXCHANGE_NEIGHBOUR, dgm.DG_EXCHANGE_TRACES):
+        s = dgm.Solver(n, p)
+        s.set_option(dgm.DG_OPT_EXCHANGE, exchange)
+        got = [s.rhs_vjp(Q, g0)]
+        for k in range(5):
+            gQ, gres = g0.clone(), r0.clone()
+            dgm.dg_rk_stage_vjp(s.ctx, k, Q, gQ, gres, 1e-3)
+            got += [gQ, gres]
+        torch.cuda.synchronize()
+        outs.append(got)
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
