@@ -132,8 +132,8 @@ int dg_set_volume_form(dg_ctx* ctx, int form);
  * DG_OPT_EXCHANGE: how an FP64 stage obtains its neighbours' face traces.
  *   DG_EXCHANGE_NEIGHBOUR (default): interpolated in the launch itself from
  *   the neighbour elements' state (read through the caches); the state is
- *   ping-ponged between the caller's Q and a workspace buffer, so a call
- *   with an odd number of stages ends with one device-to-device copy.
+ *   ping-ponged between the caller's Q and workspace buffers (a call of one
+ *   stage, dg_rk_stage, ends with a device-to-device copy).
  *   DG_EXCHANGE_TRACES: every launch writes the face traces of its updated
  *   state to a workspace buffer that the next launch reads.
  *   Both give bitwise identical results.
@@ -213,6 +213,11 @@ int dg_rhs(dg_ctx* ctx, const double* Q, double* R);
  * with the Carpenter-Kennedy (5,4) 2N-storage coefficients.  Q and res are
  * device arrays in the layout above; res is read only for s > 0. */
 int dg_rk_stage(dg_ctx* ctx, int s, double* Q, double* res, double dt);
+
+/* The same stage out of place: Qnext = Q + b_s res, Q unchanged (for callers
+ * that keep every stage's input, as a reverse pass does: no copy of the state
+ * is made before or after).  Qnext must not overlap Q or res. */
+int dg_rk_stage_to(dg_ctx* ctx, int s, const double* Q, double* Qnext, double* res, double dt);
 
 /* One LSERK45 time step (five stages) in place. */
 int dg_rk_step(dg_ctx* ctx, double* Q, double* res, double dt);

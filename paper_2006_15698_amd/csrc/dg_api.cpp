@@ -223,30 +223,55 @@ int run_reduce(dg_ctx* c, const double* Q, double out[DG_RED_VALS]) {
 
 double* q2_buf(dg_ctx* c) { return (double*)(c->ws + dg_workspace_layout(c).off_q2); }
 
-// Neighbour-read sequencing: stage g reads buf[g % 2] and writes
-// buf[(g + 1) % 2] with buf = {Q, Q2}; an odd count ends in Q2, copied back.
-// Q2 is the workspace's second state buffer unless the caller names another
-// one; with `timing` false no launch is bracketed by timing events (which are
-// created on first use).
-int stages_nb(dg_ctx* c, double* Q, double* res, double dt, int s0, int count, double* q2 = nullptr,
+// A third state buffer for the ping-pong, in the place of the two face-trace
+// buffers (60 N^2 doubles an element, at least 5 N^3 for N <= 12), which only
+// the trace-buffer exchange uses.
+double* q3_buf(dg_ctx* c) { return (double*)(c->ws + dg_workspace_layout(c).off_trace0); }
+static_assert(60 >= DG_NF * DG_MAXN, "a state fits the face-trace buffers");
+
+// Buffers of stage g of `count` ping-ponged stages on Q, with q2 and, where
+// there is one, q3 beside it: Q and q2 alternate, and the last two of an odd
+// number of stages go through q3, so that any count but one ends in Q, without
+// the copy that an odd count otherwise ends with (48^3 p=4 230 us after every
+// call of an odd number of steps, 4 us of 31 at 4^3 p=1).
+struct StagePair {
+  double *in, *out;
+};
+StagePair stage_pair(double* Q, double* q2, double* q3, int g, int count) {
+  if (q3 && (count & 1) && count > 1) {
+    if (g == count - 2) return {q2, q3};
+    if (g == count - 1) return {q3, Q};
+  }
+  return g & 1 ? StagePair{q2, Q} : StagePair{Q, q2};
+}
+
+// Copies the state back where stage_pair left it outside Q.
+int copy_back(dg_ctx* c, double* Q, const double* q2, const double* q3, int count) {
+  if (!(count & 1) || (q3 && count > 1)) return DG_OK;
+  const int err = (int)hipMemcpyAsync(Q, q2, state_bytes(c), hipMemcpyDeviceToDevice, c->stream);
+  return err ? hip_fail(err, "state copy") : DG_OK;
+}
+
+// One neighbour-read stage, in -> out.
+int launch_nb(dg_ctx* c, int s, const double* in, double* out, double* res, double dt) {
+  return c->precision == DG_FP32_MFMA
+             ? dg_launch_stage_nb_f32(c, in, out, res, 1, kRKA[s], kRKB[s], dt, s == 0)
+             : dg_launch_stage_nb(c, in, out, res, 1, kRKA[s], kRKB[s], dt, s == 0);
+}
+
+// Neighbour-read sequencing: Q ping-pongs with q2 and q3 (stage_pair), the
+// workspace's unless the caller names others; with `timing` false no launch is
+// bracketed by timing events (which are created on first use).
+int stages_nb(dg_ctx* c, double* Q, double* res, double dt, int s0, int count, double* q2, double* q3,
               bool timing = true) {
-  double* buf[2] = {Q, q2 ? q2 : q2_buf(c)};
-  int err = 0;
   for (int g = 0; g < count; ++g) {
     const int s = (s0 + g) % 5;
-    auto launch = [&] {
-      return c->precision == DG_FP32_MFMA
-                 ? dg_launch_stage_nb_f32(c, buf[g & 1], buf[(g + 1) & 1], res, 1, kRKA[s], kRKB[s], dt, s == 0)
-                 : dg_launch_stage_nb(c, buf[g & 1], buf[(g + 1) & 1], res, 1, kRKA[s], kRKB[s], dt, s == 0);
-    };
-    err = timing ? timed(c, s == 0 ? TK_STAGE_FIRST : TK_STAGE, launch) : launch();
+    const StagePair p = stage_pair(Q, q2, q3, g, count);
+    auto launch = [&] { return launch_nb(c, s, p.in, p.out, res, dt); };
+    const int err = timing ? timed(c, s == 0 ? TK_STAGE_FIRST : TK_STAGE, launch) : launch();
     if (err) return hip_fail(err, "stage launch");
   }
-  if (count & 1) {
-    err = (int)hipMemcpyAsync(Q, buf[1], state_bytes(c), hipMemcpyDeviceToDevice, c->stream);
-    if (err) return hip_fail(err, "state copy");
-  }
-  return DG_OK;
+  return copy_back(c, Q, q2, q3, count);
 }
 
 // Inviscid rate R = dQ/dt of the Euler terms: the split-form kernel, or the
@@ -257,23 +282,18 @@ int euler_rate_nb(dg_ctx* c, const double* Q, double* R) {
                                       : dg_launch_stage_nb(c, Q, nullptr, R, 0, 0.0, 0.0, 0.0, 0);
 }
 
-// Split-form stages: Q ping-pongs between Q and the workspace's second
-// state buffer like the neighbour-read stages (an odd count ends with a
-// copy back).
+// Split-form stages: Q ping-pongs as the neighbour-read stages.
 int stages_split(dg_ctx* c, double* Q, double* res, double dt, int s0, int count) {
-  double* buf[2] = {Q, q2_buf(c)};
+  double *q2 = q2_buf(c), *q3 = q3_buf(c);
   for (int g = 0; g < count; ++g) {
     const int s = (s0 + g) % 5;
+    const StagePair p = stage_pair(Q, q2, q3, g, count);
     int err = timed(c, s == 0 ? TK_STAGE_FIRST : TK_STAGE, [&] {
-      return dg_launch_split(c, buf[g & 1], buf[(g + 1) & 1], res, s == 0 ? 2 : 1, kRKA[s], kRKB[s], dt);
+      return dg_launch_split(c, p.in, p.out, res, s == 0 ? 2 : 1, kRKA[s], kRKB[s], dt);
     });
     if (err) return hip_fail(err, "split-form stage launch");
   }
-  if (count & 1) {
-    int err = (int)hipMemcpyAsync(Q, buf[1], state_bytes(c), hipMemcpyDeviceToDevice, c->stream);
-    if (err) return hip_fail(err, "state copy");
-  }
-  return DG_OK;
+  return copy_back(c, Q, q2, q3, count);
 }
 
 // Whether the viscous-flux launch forms the inviscid rate too: the FP64
@@ -311,7 +331,7 @@ int stages(dg_ctx* c, double* Q, double* res, double dt, int s0, int count) {
   const bool f32 = c->precision == DG_FP32_MFMA;
   if (c->mu > 0.0) return stages_visc(c, Q, res, dt, s0, count);
   if (c->volume_form == DG_VOLUME_KEP) return stages_split(c, Q, res, dt, s0, count);
-  if (c->exchange == DG_EXCHANGE_NEIGHBOUR) return stages_nb(c, Q, res, dt, s0, count);
+  if (c->exchange == DG_EXCHANGE_NEIGHBOUR) return stages_nb(c, Q, res, dt, s0, count, q2_buf(c), q3_buf(c));
   int err = timed(c, TK_TRACE, [&] {
     return f32 ? dg_launch_trace_f32(c, Q, (char*)trace_buf(c, 0)) : dg_launch_trace(c, Q, trace_buf(c, 0));
   });
@@ -512,7 +532,7 @@ dg_ctx* dg_create(int nx, int ny, int nz, int p, double gamma) {
   c->epoch = 1;
   c->gstream = nullptr;
   c->ev_in = c->ev_out = nullptr;
-  c->gexec[0] = c->gexec[1] = nullptr;
+  for (hipGraphExec_t& x : c->gexec) x = nullptr;
   c->gQ = c->gR = nullptr;
   c->gdt = 0.0;
   c->gepoch = 0;
@@ -524,8 +544,8 @@ dg_ctx* dg_create(int nx, int ny, int nz, int p, double gamma) {
 void dg_destroy(dg_ctx* c) {
   if (!c) return;
   delete (DGTiming*)c->timing;
-  for (int k = 0; k < 2; ++k)
-    if (c->gexec[k]) (void)hipGraphExecDestroy(c->gexec[k]);
+  for (hipGraphExec_t x : c->gexec)
+    if (x) (void)hipGraphExecDestroy(x);
   if (c->ev_in) (void)hipEventDestroy(c->ev_in);
   if (c->ev_out) (void)hipEventDestroy(c->ev_out);
   if (c->gstream) (void)hipStreamDestroy(c->gstream);
@@ -759,6 +779,26 @@ int dg_rk_stage(dg_ctx* c, int s, double* Q, double* res, double dt) {
   return stages(c, Q, res, dt, s, 1);
 }
 
+int dg_rk_stage_to(dg_ctx* c, int s, const double* Q, double* Qnext, double* res, double dt) {
+  int rc = check_ready(c);
+  if (rc) return rc;
+  if (s < 0 || s > 4) return fail(DG_EINVAL, "stage must be 0..4 (got %d)", s);
+  if (!std::isfinite(dt)) return fail(DG_EINVAL, "dt must be finite");
+  rc = check_state_pair(c, Qnext, "Qnext", res, "res");
+  if (rc) return rc;
+  rc = check_state_pair(c, Q, "Q", res, "res");
+  if (rc) return rc;
+  rc = check_state_pair(c, Q, "Q", Qnext, "Qnext");
+  if (rc) return rc;
+  if (c->exchange == DG_EXCHANGE_NEIGHBOUR && c->mu == 0.0 && c->volume_form == DG_VOLUME_STANDARD) {
+    const int err = timed(c, s == 0 ? TK_STAGE_FIRST : TK_STAGE, [&] { return launch_nb(c, s, Q, Qnext, res, dt); });
+    return err ? hip_fail(err, "stage launch") : DG_OK;
+  }
+  const int err = (int)hipMemcpyAsync(Qnext, Q, state_bytes(c), hipMemcpyDeviceToDevice, c->stream);
+  if (err) return hip_fail(err, "state copy");
+  return stages(c, Qnext, res, dt, s, 1);
+}
+
 int dg_rk_steps(dg_ctx* c, double* Q, double* res, double dt, int nsteps) {
   int rc = check_ready(c);
   if (rc) return rc;
@@ -790,7 +830,9 @@ int dg_rk_steps_noalloc(dg_ctx* c, double* Q, double* res, double dt, int nsteps
   double* q2 = nullptr;
   rc = scratch_of_current_device(&q2);
   if (rc) return rc;
-  return stages_nb(c, Q, res, dt, 0, 5 * nsteps, q2, false);
+  // the static buffer holds the third state too where two fit
+  double* q3 = 2 * state_bytes(c) <= kScratchBytes ? q2 + state_bytes(c) / sizeof(double) : nullptr;
+  return stages_nb(c, Q, res, dt, 0, 5 * nsteps, q2, q3, false);
 }
 
 int dg_rk_graph_steps(dg_ctx* c, double* Q, double* res, double dt, int nsteps) {
@@ -813,9 +855,9 @@ int dg_rk_graph_steps(dg_ctx* c, double* Q, double* res, double dt, int nsteps) 
     if (err) return hip_fail(err, "graph event");
   }
   if (c->gQ != Q || c->gR != res || c->gdt != dt || c->gepoch != c->epoch) {
-    for (int k = 0; k < 2; ++k) {
-      if (c->gexec[k]) (void)hipGraphExecDestroy(c->gexec[k]);
-      c->gexec[k] = nullptr;
+    for (hipGraphExec_t& x : c->gexec) {
+      if (x) (void)hipGraphExecDestroy(x);
+      x = nullptr;
     }
   }
   // the graph stream runs after the caller's stream, and the caller's
@@ -824,21 +866,20 @@ int dg_rk_graph_steps(dg_ctx* c, double* Q, double* res, double dt, int nsteps) 
   if (err) return hip_fail(err, "event record");
   err = (int)hipStreamWaitEvent(c->gstream, c->ev_in, 0);
   if (err) return hip_fail(err, "stream wait");
-  double* buf[2] = {Q, q2_buf(c)};
-  for (int par = 0; par < 2; ++par) {
-    if (c->gexec[par]) continue;
-    // one step = five stage launches; a step that starts from buf[par]
-    // (stage count before it of parity par) alternates from there
+  // step graphs: 0 from Q to the second buffer, 1 back, and 2, the last of an
+  // odd number of steps, from Q to Q by way of the third (stage_pair)
+  double *q2 = q2_buf(c), *q3 = q3_buf(c);
+  for (int par = 0; par < 3; ++par) {
+    const bool used = par == 2 ? (nsteps & 1) != 0 : nsteps > 1;
+    if (c->gexec[par] || !used) continue;
     hipGraph_t graph = nullptr;
     const hipStream_t user = c->stream;
     c->stream = c->gstream;
     err = (int)hipStreamBeginCapture(c->gstream, hipStreamCaptureModeThreadLocal);
     int lerr = 0;
     for (int s = 0; s < 5 && !err && !lerr; ++s) {
-      const int g = par + s;
-      lerr = c->precision == DG_FP32_MFMA
-                 ? dg_launch_stage_nb_f32(c, buf[g & 1], buf[(g + 1) & 1], res, 1, kRKA[s], kRKB[s], dt, s == 0)
-                 : dg_launch_stage_nb(c, buf[g & 1], buf[(g + 1) & 1], res, 1, kRKA[s], kRKB[s], dt, s == 0);
+      const StagePair p = par == 2 ? stage_pair(Q, q2, q3, s, 5) : stage_pair(Q, q2, nullptr, par + s, 0);
+      lerr = launch_nb(c, s, p.in, p.out, res, dt);
     }
     const int cerr = err ? err : (int)hipStreamEndCapture(c->gstream, &graph);
     c->stream = user;
@@ -856,12 +897,8 @@ int dg_rk_graph_steps(dg_ctx* c, double* Q, double* res, double dt, int nsteps) 
   c->gdt = dt;
   c->gepoch = c->epoch;
   for (int n = 0; n < nsteps; ++n) {
-    err = (int)hipGraphLaunch(c->gexec[n & 1], c->gstream);
+    err = (int)hipGraphLaunch(c->gexec[(nsteps & 1) && n == nsteps - 1 ? 2 : n & 1], c->gstream);
     if (err) return hip_fail(err, "graph launch");
-  }
-  if (nsteps & 1) {
-    err = (int)hipMemcpyAsync(Q, buf[1], state_bytes(c), hipMemcpyDeviceToDevice, c->gstream);
-    if (err) return hip_fail(err, "state copy");
   }
   err = (int)hipEventRecord(c->ev_out, c->gstream);
   if (err) return hip_fail(err, "event record");

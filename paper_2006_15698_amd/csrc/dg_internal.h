@@ -61,12 +61,12 @@ struct dg_ctx {
   double mu, prandtl, kappa;
   int volume_form;  // DG_VOLUME_STANDARD or DG_VOLUME_KEP (dg_set_volume_form)
   // graph replay of whole steps (dg_rk_graph_steps): one executable graph
-  // per ping-pong parity, valid while the arrays, dt and `epoch` (bumped by
+  // per place of a step in the ping-pong, valid while the arrays, dt and `epoch` (bumped by
   // every setter that changes what a launch does) are unchanged
   unsigned epoch;
   hipStream_t gstream;
   hipEvent_t ev_in, ev_out;
-  hipGraphExec_t gexec[2];
+  hipGraphExec_t gexec[3];
   const double* gQ;
   const double* gR;
   double gdt;

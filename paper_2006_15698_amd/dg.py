@@ -78,6 +78,7 @@ _SIGS = {
     "dg_quadrature": (_i, [_i, _dp, _dp]),
     "dg_rhs": (_i, [_vp, _vp, _vp]),
     "dg_rk_stage": (_i, [_vp, _i, _vp, _vp, _d]),
+    "dg_rk_stage_to": (_i, [_vp, _i, _vp, _vp, _vp, _d]),
     "dg_rk_step": (_i, [_vp, _vp, _vp, _d]),
     "dg_rk_steps": (_i, [_vp, _vp, _vp, _d, _i]),
     "dg_rk_graph_steps": (_i, [_vp, _vp, _vp, _d, _i]),
@@ -252,6 +253,11 @@ def dg_rhs(ctx, Q, R):
 def dg_rk_stage(ctx, s, Q, res, dt):
     nd = _nd(ctx)
     return _check(_lib.dg_rk_stage(ctx, int(s), _ptr(Q, nd), _ptr(res, nd), float(dt)))
+
+
+def dg_rk_stage_to(ctx, s, Q, Qnext, res, dt):
+    nd = _nd(ctx)
+    return _check(_lib.dg_rk_stage_to(ctx, int(s), _ptr(Q, nd), _ptr(Qnext, nd), _ptr(res, nd), float(dt)))
 
 
 def dg_rk_step(ctx, Q, res, dt):
@@ -797,7 +803,8 @@ def rk_gradient(solver, Q0, dt, nsteps, objective_grad, every=8):
     objective_grad(Q) must return dJ/dQ at the final state.  Forward: one
     pass storing Q at every ``every``-th step.  Reverse, segment by segment:
     recompute the 25..40 stage inputs of the segment from its checkpoint
-    (dg_rk_stage, bitwise equal to the forward pass), then run the stages
+    (dg_rk_stage_to, bitwise equal to the forward pass; the segment's last
+    stage is left out, as nothing reads its output), then run the stages
     backwards through dg_rk_stage_vjp.  Returns (J-gradient, final state)."""
     ckpts = []
     Q = Q0.detach().clone()
@@ -813,13 +820,16 @@ def rk_gradient(solver, Q0, dt, nsteps, objective_grad, every=8):
     for seg in reversed(range(len(ckpts))):
         n0 = seg * every
         n1 = min(n0 + every, nsteps)
-        Q = ckpts[seg].clone()
+        Q = ckpts[seg]
         res = torch.zeros_like(Q)
         inputs = []
         for n in range(n0, n1):
             for s in range(5):
-                inputs.append((s, Q.clone()))
-                solver.rk_stage(s, Q, res, dt)
+                inputs.append((s, Q))
+                if n < n1 - 1 or s < 4:
+                    Qnext = torch.empty_like(Q)
+                    dg_rk_stage_to(solver.ctx, s, Q, Qnext, res, dt)
+                    Q = Qnext
         for s, Qs in reversed(inputs):
             dg_rk_stage_vjp(solver.ctx, s, Qs, gQ, gres, dt)
     return gQ, Qfinal

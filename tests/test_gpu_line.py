@@ -147,3 +147,36 @@ def test_reverse_stage_bitwise(dgm, p, n):
         outs.append(got)
     for a, b in zip(*outs):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("form", ["euler", "fp32", "kep", "viscous"])
+@pytest.mark.parametrize("p,n", [(1, (5, 3, 4)), (4, (3, 13, 21))])
+def test_odd_stage_counts_and_stage_to(dgm, form, p, n):
+    """Calls of one, two, three and five steps (the odd ones end by way of the
+    third state buffer), graph replay of each, and the out-of-place stage: all
+    bitwise those of the stages one by one in place."""
+    import torch
+    print(f"[odd stage counts {form} p={p} n={n}]", flush=True)
+    s = dgm.Solver(n, p, precision=dgm.DG_FP32_MFMA if form == "fp32" else dgm.DG_FP64,
+                   mu=0.01 if form == "viscous" else 0.0,
+                   volume_form=dgm.DG_VOLUME_KEP if form == "kep" else dgm.DG_VOLUME_STANDARD)
+    Q0 = torch.from_numpy(W.random_smooth(n, p, seed=95, noise=0.01)).cuda()
+    dt = 0.1 * s.dt_cfl(Q0, 1.0)
+    for nsteps in (1, 2, 3, 5):
+        Q, res, Qt, rest = Q0.clone(), torch.zeros_like(Q0), Q0.clone(), torch.zeros_like(Q0)
+        for _ in range(nsteps):
+            for k in range(5):
+                s.rk_stage(k, Q, res, dt)
+                nxt = torch.full_like(Q0, float("nan"))
+                dgm.dg_rk_stage_to(s.ctx, k, Qt, nxt, rest, dt)
+                Qt = nxt
+        ends = [(Qt, rest)]
+        for graph in (False, True, True):
+            Qg, resg = Q0.clone(), torch.zeros_like(Q0)
+            s.step(Qg, resg, dt, nsteps, graph=graph)
+            ends.append((Qg, resg))
+        torch.cuda.synchronize()
+        for a, b in ends:
+            assert torch.equal(a, Q) and torch.equal(b, res), nsteps
+    with pytest.raises(dgm.DGError):
+        dgm.dg_rk_stage_to(s.ctx, 0, Q0, Q0, torch.zeros_like(Q0), dt)
