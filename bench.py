@@ -100,11 +100,14 @@ STAGE_SOURCES = {
     "batch": _COMMON_SOURCES + _FP32_SOURCES + ["paper_2006_15698_amd/csrc/dg_batch.h",
                                                 "paper_2006_15698_amd/csrc/kern_batch.hip",
                                                 "paper_2006_15698_amd/csrc/batch_api.cpp"],
-    "vjp": _COMMON_SOURCES + ["paper_2006_15698_amd/csrc/kern_vjp.hip"],
+    "vjp": _COMMON_SOURCES + ["paper_2006_15698_amd/csrc/kern_vjp.hip",
+                              "paper_2006_15698_amd/csrc/kern_vjp_line.hip",
+                              "paper_2006_15698_amd/csrc/vjp_dev.h"],
     "visc": _COMMON_SOURCES + ["paper_2006_15698_amd/csrc/kern_visc.hip",
                                "paper_2006_15698_amd/csrc/kern_visc_line.hip"],
     "split": _COMMON_SOURCES + ["paper_2006_15698_amd/csrc/kern_split.hip"],
     "varp": _COMMON_SOURCES + ["paper_2006_15698_amd/csrc/dg_varp.h", "paper_2006_15698_amd/csrc/kern_varp.hip",
+                               "paper_2006_15698_amd/csrc/kern_varp_line.hip",
                                "paper_2006_15698_amd/csrc/kern_varp_hang.hip",
                                "paper_2006_15698_amd/csrc/varp_api.cpp"],
 }
@@ -523,7 +526,7 @@ def varp_roofline(v, Q, res, dt, K, nodes, faces, workload):
     return {"bound": "hbm", "achieved": dom["achieved"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": dom["achieved"] / HBM_PEAK_GBS,
             "traffic": measured_traffic(workload, "varp", {}),
-            "kernel": f"k_varp<{pdom + 1}> (degree {pdom}: fused RHS + LSERK45 stage, stages 2..5)",
+            "kernel": f"{'k_varp_line' if 1 <= pdom <= 6 else 'k_varp'}<{pdom + 1}> (degree {pdom}: fused RHS + LSERK45 stage, stages 2..5)",
             "avg_launch_us": dom["avg_launch_us"], "launches": dom["launches"],
             "alg_bytes_per_launch": dom["alg_bytes_per_launch"], "kernels": kernels,
             "stage_bytes_per_node": ALG_BYTES_PER_DOF_STAGE}

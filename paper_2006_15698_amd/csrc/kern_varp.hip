@@ -30,7 +30,9 @@
 //   lower side into the face-flux buffer.
 // k_varp_hanging (kern_varp_hang.hip): one workgroup per coarse face with
 //   hanging faces, one wave per quarter.
-// k_varp<N, MODE, TR>: a workgroup owns EPB elements of one degree and size from
+// k_varp_line<N, MODE, TR> (kern_varp_line.hip): the stage of a group with one
+//   thread per line of nodes, at p = 1, 2 and for all but small groups at p = 3..6.
+// k_varp<N, MODE, TR>, for the rest: a workgroup owns EPB elements of one degree and size from
 // that group's element list (in pencil order; each XCD takes a contiguous
 // part), one thread per node:
 //   A. the elements' states into LDS (each element's nodes are contiguous);
@@ -57,8 +59,8 @@ namespace {
 template <int N>
 struct VCfg {
   // elements per workgroup and threads (one per node, whole waves); the
-  // single-degree kernel's tiles from N = 3 on (at most 64 face tasks)
-  static constexpr int EPB = N <= 2 ? 8 : (N == 3 ? 9 : (N == 4 ? 4 : (N == 5 ? 2 : 1)));
+  // single-degree kernel's tiles (at most 64 face tasks)
+  static constexpr int EPB = N == 1 ? 8 : (N == 4 ? 4 : (N == 5 ? 2 : 1));
   static constexpr int NODES = EPB * N * N * N;
   static constexpr int NT = (NODES + 63) / 64 * 64;
   static constexpr int NW = NT / 64;
@@ -67,11 +69,8 @@ struct VCfg {
   static constexpr int WPF = (FP + 63) / 64;     // 64-point slots per face
   static constexpr int SMEM = 5 * NODES + 30 * FP + N * N + 2 * N;
   // the new state of a stage that writes its traces: a region of its own
-  // (written in the output phase, one barrier before the traces), except
-  // at N = 3, where it would cost a workgroup per CU (the state's region is
-  // reused after a barrier instead)
-  static constexpr bool OWN_NEW = N != 3;
-  static constexpr int SMEM_TR = SMEM + (OWN_NEW ? 5 * NODES : 0);
+  // (written in the output phase, one barrier before the traces)
+  static constexpr int SMEM_TR = SMEM + 5 * NODES;
   static_assert(TASKS <= 64, "the face tasks are looked up by one wave");
 };
 
@@ -446,8 +445,7 @@ __global__ void __launch_bounds__(VCfg<N>::NT) __attribute__((amdgpu_waves_per_e
     //      fbuf, for the next stage's face launches (the same chain as the
     //      face kernels' traces from the state, so the same values)
     if (TR && sAny) {
-      double* sN = C::OWN_NEW ? smem + C::SMEM : sQ;
-      if (!C::OWN_NEW) __syncthreads();   // the volume phase has read sF
+      double* sN = smem + C::SMEM;
       if (nthr) {
 #pragma unroll
         for (int f = 0; f < 5; ++f) sN[f * NODES + tid] = q[f];
@@ -499,29 +497,14 @@ int launch_varp_n(hipStream_t stream, const DGTables& tb, const DGVarpMesh& m, i
 }  // namespace
 }  // namespace dgdev
 
-int dg_varp_epb(int N) {
-  using namespace dgdev;
-  switch (N) {
-    case 1: return VCfg<1>::EPB;
-    case 2: return VCfg<2>::EPB;
-    case 3: return VCfg<3>::EPB;
-    case 4: return VCfg<4>::EPB;
-    case 5: return VCfg<5>::EPB;
-    case 6: return VCfg<6>::EPB;
-    case 7: return VCfg<7>::EPB;
-    case 8: return VCfg<8>::EPB;
-    default: return 0;
-  }
-}
-
 int dg_launch_varp(hipStream_t stream, int N, const DGTables& tb, const DGVarpMesh& m, int first, int count,
                    const double* Qin, double* Qout, double* RR, int mode, double a, double b, double dt, bool traces) {
   using namespace dgdev;
+  if (dg_varp_line_pays(N, count))
+    return dg_launch_varp_line(stream, N, tb, m, first, count, Qin, Qout, RR, mode, a, b, dt, traces);
 #define CALL(n) launch_varp_n<n>(stream, tb, m, first, count, Qin, Qout, RR, mode, a, b, dt, traces && mode != 0)
   switch (N) {
     case 1: return CALL(1);
-    case 2: return CALL(2);
-    case 3: return CALL(3);
     case 4: return CALL(4);
     case 5: return CALL(5);
     case 6: return CALL(6);

@@ -117,11 +117,43 @@ __device__ __forceinline__ void add_line(double* x, const int (&o)[N], double c,
   for (int m = 0; m < N; ++m) x[o[m]] = fma(c, v[m], r[m]);
 }
 
-// The standard form's rate of direction D on the thread's line
-// q[field][node]: volume contraction plus the lift of the two Lax-Friedrichs
-// fluxes, handed to `emit(f, s)` for every field (2/h_D times s[node] is the
-// rate) of an active lane, after `pre()` on every lane.  tl, tr: the
-// line's own end traces; nl, nr: the - and + neighbour's traces.
+// Volume contraction of direction D on the thread's line q[field][node] plus
+// the lift of its two face fluxes fl, fr, handed to `emit(f, s)` for every
+// field (2/h_D times s[node] is the rate).
+template <int N, int D, class Emit>
+__device__ __forceinline__ void line_rate(const LineTables<N>& t, const double (&q)[5][N], const double* fl,
+                                          const double* fr, Emit&& emit) {
+  double pr[N], ud[N];
+#pragma unroll
+  for (int a = 0; a < N; ++a) {
+    const double rinv = recip(q[0][a]);
+    pr[a] = t.tb.gm1 * (q[4][a] - 0.5 * (q[1][a] * q[1][a] + q[2][a] * q[2][a] + q[3][a] * q[3][a]) * rinv);
+    ud[a] = q[1 + D][a] * rinv;
+  }
+#pragma unroll
+  for (int f = 0; f < 5; ++f) {
+    double F[N], s[N];
+#pragma unroll
+    for (int a = 0; a < N; ++a) {
+      if (f == 0) F[a] = q[1 + D][a];
+      else if (f == 4) F[a] = (q[4][a] + pr[a]) * ud[a];
+      else F[a] = q[f][a] * ud[a] + (D == f - 1 ? pr[a] : 0.0);
+    }
+#pragma unroll
+    for (int m = 0; m < N; ++m) {
+      double v = 0.0;
+#pragma unroll
+      for (int a = 0; a < N; ++a) v = fma(t.dh(m, a), F[a], v);
+      v = fma(t.liftm(m), fl[f], v);
+      s[m] = fma(-t.liftp(m), fr[f], v);
+    }
+    emit(f, s);
+  }
+}
+
+// The standard form's rate of direction D: line_rate with the two
+// Lax-Friedrichs fluxes, on an active lane, after `pre()` on every lane.
+// tl, tr: the line's own end traces; nl, nr: the - and + neighbour's traces.
 template <int N>
 struct EulerLine {
   static constexpr bool BULK = false;   // rates are handed out field by field
@@ -132,34 +164,10 @@ struct EulerLine {
     const LineTables<N>& t = tab;
     pre();
     if (!act) return;
-    double fl[5], fr[5], pr[N], ud[N];
+    double fl[5], fr[5];
     lf_flux_d<D>(nl, tl, t.tb.gamma, t.tb.gm1, fl);
     lf_flux_d<D>(tr, nr, t.tb.gamma, t.tb.gm1, fr);
-#pragma unroll
-    for (int a = 0; a < N; ++a) {
-      const double rinv = recip(q[0][a]);
-      pr[a] = t.tb.gm1 * (q[4][a] - 0.5 * (q[1][a] * q[1][a] + q[2][a] * q[2][a] + q[3][a] * q[3][a]) * rinv);
-      ud[a] = q[1 + D][a] * rinv;
-    }
-#pragma unroll
-    for (int f = 0; f < 5; ++f) {
-      double F[N], s[N];
-#pragma unroll
-      for (int a = 0; a < N; ++a) {
-        if (f == 0) F[a] = q[1 + D][a];
-        else if (f == 4) F[a] = (q[4][a] + pr[a]) * ud[a];
-        else F[a] = q[f][a] * ud[a] + (D == f - 1 ? pr[a] : 0.0);
-      }
-#pragma unroll
-      for (int m = 0; m < N; ++m) {
-        double v = 0.0;
-#pragma unroll
-        for (int a = 0; a < N; ++a) v = fma(t.dh(m, a), F[a], v);
-        v = fma(t.liftm(m), fl[f], v);
-        s[m] = fma(-t.liftp(m), fr[f], v);
-      }
-      emit(f, s);
-    }
+    line_rate<N, D>(t, q, fl, fr, emit);
   }
 };
 

@@ -6,6 +6,7 @@ leave short blocks, one-element rows (an element its own x-neighbour), whole
 and left-over parts of the XCD-shared slabs, and arrays that start at an odd
 multiple of 8 bytes."""
 
+import numpy as np
 import pytest
 
 import workloads as W
@@ -180,3 +181,44 @@ def test_odd_stage_counts_and_stage_to(dgm, form, p, n):
             assert torch.equal(a, Q) and torch.equal(b, res), nsteps
     with pytest.raises(dgm.DGError):
         dgm.dg_rk_stage_to(s.ctx, 0, Q0, Q0, torch.zeros_like(Q0), dt)
+
+
+@pytest.mark.parametrize("p,other,refined", [(3, 2, True), (4, 5, True), (4, 4, True), (5, 0, False), (5, 6, True),
+                                             (6, 7, True)])
+def test_variable_degree_groups_bitwise(dgm, p, other, refined):
+    """A mesh of two degrees, some cells refined, against the same mesh tiled
+    periodically: the elements of the small one run with a thread per node,
+    the tiled one's groups of degree p are large enough for a thread per line.
+    The rate and two steps (with the face traces handed on between stages)
+    agree bit for bit in every copy."""
+    import torch
+    print(f"[varp lines p={p} other={other} refined={refined}]", flush=True)
+    tile, n = (4, 4, 2), (5, 4, 5)
+    rng = np.random.default_rng(820 + p)
+    ref = (rng.random((n[2], n[1], n[0])) < 0.15).astype(int) * int(refined)
+    count = np.where(ref == 1, 8, 1)
+    deg = [np.where(rng.random(c) < 0.85, p, other) for c in count.reshape(-1)]
+    q = [np.stack([1.0 + 0.1 * rng.random((d + 1) ** 3), *(0.2 * rng.random((3, (d + 1) ** 3))),
+                   2.5 + 0.1 * rng.random((d + 1) ** 3)]) for cell in deg for d in cell]
+    first = np.concatenate([[0], np.cumsum(count.reshape(-1))])
+
+    def mesh(t):
+        m = tuple(a * b for a, b in zip(n, t))
+        cells = [(cz % n[2] * n[1] + cy % n[1]) * n[0] + cx % n[0]
+                 for cz in range(m[2]) for cy in range(m[1]) for cx in range(m[0])]
+        elems = np.concatenate([np.arange(first[c], first[c + 1]) for c in cells])
+        r = np.tile(ref, t[::-1])
+        v = dgm.VariableDegree(m, np.concatenate([deg[c] for c in cells]), L=tuple(float(x) for x in t),
+                               refine=r if refined else None)
+        Q = torch.from_numpy(np.concatenate([q[e] for e in elems], axis=1).reshape(-1)).cuda()
+        res = torch.zeros_like(Q)
+        out = [v.rhs(Q).clone()]
+        v.step(Q, res, 2e-4, nsteps=2)
+        torch.cuda.synchronize()
+        return elems, [x.cpu().numpy().reshape(5, -1) for x in out + [Q, res]], v.offsets
+
+    _, small, off = mesh((1, 1, 1))
+    elems, tiled, _ = mesh(tile)
+    at = np.concatenate([np.arange(off[e], off[e + 1]) for e in elems])
+    for a, b in zip(small, tiled):
+        assert np.isfinite(a).all() and np.array_equal(b, a[:, at])
