@@ -5,11 +5,13 @@
 // a workgroup is one wave, the 1-D tables sit in scalar registers.  What
 // differs is where a line's neighbours are: the elements of a workgroup are
 // any entries of the group's list, and a face either has a neighbour of the
-// same size and degree (its state is read along the normal line, as for any
-// other face: also by a lane whose neighbour is in the same workgroup) or a
-// projected flux in the face-flux buffer.  Both are read by the same loads:
-// for a flux the field stride is that of the buffer and the stride along the
-// line is 0, so that a wave whose lanes differ has no branch to wait at.
+// same size and degree (its state is read along the normal line, also where
+// the neighbour is in the same workgroup) or a projected flux in the face-flux
+// buffer.  A lane whose face has a flux reads a line of its own element like
+// the others, so that those loads keep their constant strides (offsets of the
+// instruction; with strides per lane 48^3 p = 4 took 646 us a stage against
+// 635, 32^3 p = 6 602 against 552) and no branch,
+// and the blocks with such a face fetch the fluxes afterwards.
 
 #include "dg_varp.h"
 #include "stage_line.h"
@@ -44,7 +46,8 @@ k_varp_line(const DGTables tb, const DGVarpMesh mesh, int first, int count, cons
   static_assert(N >= 2 && FP <= 64 && 2 * LinePairs<N, EPB>::LPF <= 64, "one line and one pair per lane");
   __shared__ __align__(16) double smem[LineSmem<N, EPB>::size];
   __shared__ long long sOff[EPB];
-  __shared__ long long sFace[TASKS];   // [face][element]
+  __shared__ long long sFace[TASKS];   // [face][element] the face table's entries
+  __shared__ long long sNb[TASKS];     // the neighbours' first nodes (own, where the face has a flux)
   double* sS = smem;             // [5][SF] state
   double* sA = smem + 5 * SF;    // [5][SF] rate
   double* sT = sA;               // [2][5][FP] neighbour traces or fluxes, before the rate is first written
@@ -58,15 +61,17 @@ k_varp_line(const DGTables tb, const DGVarpMesh mesh, int first, int count, cons
 
   // ---- A: the block's places in the state and its faces (absent elements
   //         repeat the last one)
-  bool any = false;
+  bool any = false;   // a face of the block has a flux
 #pragma unroll
   for (int i = 0; i < (TASKS + 63) / 64; ++i) {
     const int t = imin(lane + 64 * i, TASKS - 1);
     const int face = t / EPB, fel = t - face * EPB;
     const int e = mesh.list[first + blk0 + imin(fel, ne - 1)];
     const VFace fc{mesh.face[(int64_t)e * 6 + face]};
-    if (i == 0 && lane < EPB) sOff[lane] = mesh.off[e];
+    const long long off = mesh.off[e];
+    if (i == 0 && lane < EPB) sOff[lane] = off;
     sFace[t] = fc.raw;
+    sNb[t] = fc.flux() ? off : fc.place();
     any = any || __ballot(fc.flux()) != 0ull;
   }
   __syncthreads();
@@ -92,25 +97,21 @@ k_varp_line(const DGTables tb, const DGVarpMesh mesh, int first, int count, cons
   const int ln = imin(lane, FP - 1);
   const int el = ln / N2, pt = ln - el * N2;
   const int b = pt / N, a = pt - b * N;
-  // the x-neighbours' lines, or the pair of flux points that holds this one
+  // the x-neighbours' lines
   double xo[2][5][N];
 #pragma unroll
   for (int s = 0; s < 2; ++s) {
-    const VFace fc{sFace[s * EPB + el]};
-    const double* xb = fc.flux() ? mesh.fbuf + fc.place() + imin(pt, N2 - 2) : Qin + fc.place() + pt * N;
-    const int64_t fs = fc.flux() ? N2 : T;
-    const int ms = fc.flux() ? 0 : 1;
+    const double* xb = Qin + sNb[s * EPB + el] + pt * N;
 #pragma unroll
     for (int f = 0; f < 5; ++f) {
 #pragma unroll
       for (int h = 0; h < N / 2; ++h) {
         double2 v;
-        __builtin_memcpy(&v, xb + 2 * h * ms, 16);
+        __builtin_memcpy(&v, xb + f * T + 2 * h, 16);
         xo[s][f][2 * h] = v.x;
         xo[s][f][2 * h + 1] = v.y;
       }
-      if (N % 2) xo[s][f][N - 1] = xb[(N - 1) * ms];
-      xb += fs;
+      if (N % 2) xo[s][f][N - 1] = xb[f * T + N - 1];
     }
   }
   __builtin_amdgcn_sched_barrier(0);
@@ -125,38 +126,20 @@ k_varp_line(const DGTables tb, const DGVarpMesh mesh, int first, int count, cons
   }
   __builtin_amdgcn_sched_barrier(0);
 
-  // ---- B: the neighbours' traces (or the faces' fluxes).  On the y- and
-  //         z-faces a lane forms those of a pair of points, which change
-  //         lanes through sT; each consumed field of the x- and y-lines
-  //         issues the field of the y- and z-lines that takes its registers.
+  // ---- B: the neighbours' traces.  On the y- and z-faces a lane forms those
+  //         of a pair of points, which change lanes through sT; each consumed
+  //         field of the x- and y-lines issues the field of the y- and z-lines
+  //         that takes its registers.
   const PairLane<N, EPB> pl(imin(lane, 2 * LinePairs<N, EPB>::LPF - 1));
   const bool paired = lane < 2 * LinePairs<N, EPB>::LPF;
-  const VFace fy{sFace[(2 + pl.side) * EPB + pl.fel]}, fz{sFace[(4 + pl.side) * EPB + pl.fel]};
-  const double* yb = fy.flux() ? mesh.fbuf + fy.place() + pl.pt : Qin + fy.place() + tnode<N>(1, 0, pl.pt);
-  const double* zb = fz.flux() ? mesh.fbuf + fz.place() + pl.pt : Qin + fz.place() + tnode<N>(2, 0, pl.pt);
-  const int64_t yfs = fy.flux() ? N2 : T, zfs = fz.flux() ? N2 : T;
-  const int yms = fy.flux() ? 0 : N, zms = fz.flux() ? 0 : N2;
+  const double* yb = Qin + sNb[(2 + pl.side) * EPB + pl.fel] + tnode<N>(1, 0, pl.pt);
+  const double* zb = Qin + sNb[(4 + pl.side) * EPB + pl.fel] + tnode<N>(2, 0, pl.pt);
   double* pT = sT + pl.side * 5 * FP + pl.fel * N2 + pl.pt;
   double pc[N];
 #pragma unroll
   for (int m = 0; m < N; ++m) pc[m] = pl.side ? tab.lm(m) : tab.lp(m);
   double2 w[5][N];
-  auto load_pairs = [&](const double*& p, int64_t fs, int ms, double2(&v)[N]) {
-#pragma unroll
-    for (int m = 0; m < N; ++m) __builtin_memcpy(&v[m], p + m * ms, 16);
-    p += fs;
-  };
-  auto store_pairs = [&](int f, bool flux) {
-    double h[2];
-    store_pair_trace<N>(w[f], pc, h);
-    pT[f * FP] = flux ? w[f][0].x : h[0];
-    pT[f * FP + 1] = flux ? w[f][0].y : h[1];
-  };
   double q[5][N], tl[5], tr[5], nl[3][5], nr[3][5];
-  const bool ml[3] = {VFace{sFace[0 * EPB + el]}.flux(), VFace{sFace[2 * EPB + el]}.flux(),
-                      VFace{sFace[4 * EPB + el]}.flux()};
-  const bool mr[3] = {VFace{sFace[1 * EPB + el]}.flux(), VFace{sFace[3 * EPB + el]}.flux(),
-                      VFace{sFace[5 * EPB + el]}.flux()};
   auto take = [&](int d) {
     __syncthreads();
 #pragma unroll
@@ -174,34 +157,50 @@ k_varp_line(const DGTables tb, const DGVarpMesh mesh, int first, int count, cons
       u = fma(tab.lp(m), xo[0][f][m], u);   // left neighbour: its right end
       v = fma(tab.lm(m), xo[1][f][m], v);   // right neighbour: its left end
     }
-    u = ml[0] ? (pt == N2 - 1 ? xo[0][f][1] : xo[0][f][0]) : u;
-    v = mr[0] ? (pt == N2 - 1 ? xo[1][f][1] : xo[1][f][0]) : v;
     asm volatile("" : "+v"(u), "+v"(v));   // formed here, before the y-line takes the registers
     nl[0][f] = u;
     nr[0][f] = v;
-    load_pairs(yb, yfs, yms, w[f]);
+    load_pair_line<N, 1>(yb + f * T, w[f]);
     __builtin_amdgcn_sched_barrier(0);
   }
   __syncthreads();
 #pragma unroll
   for (int f = 0; f < 5; ++f) {
-    if (paired) store_pairs(f, fy.flux());
-    load_pairs(zb, zfs, zms, w[f]);
+    if (paired) store_pair_trace<N>(w[f], pc, pT + f * FP);
+    load_pair_line<N, 2>(zb + f * T, w[f]);
     __builtin_amdgcn_sched_barrier(0);
   }
   take(1);
 #pragma unroll
   for (int f = 0; f < 5; ++f) {
-    if (paired) store_pairs(f, fz.flux());
+    if (paired) store_pair_trace<N>(w[f], pc, pT + f * FP);
   }
   take(2);
+  // faces that have a flux take it in the neighbour's trace's place
+  bool ml[3] = {}, mr[3] = {};
+  if (any) {
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      const VFace fl{sFace[2 * d * EPB + el]}, fr{sFace[(2 * d + 1) * EPB + el]};
+      ml[d] = fl.flux();
+      mr[d] = fr.flux();
+      if (ml[d]) {
+#pragma unroll
+        for (int f = 0; f < 5; ++f) nl[d][f] = mesh.fbuf[fl.place() + f * N2 + pt];
+      }
+      if (mr[d]) {
+#pragma unroll
+        for (int f = 0; f < 5; ++f) nr[d][f] = mesh.fbuf[fr.place() + f * N2 + pt];
+      }
+    }
+  }
 
   // ---- C: the three directions, summed through sA in the order x, y, z
-  auto line = [&](auto dir, int o0, int os) {
+  auto line = [&](auto dir) {
     constexpr int D = decltype(dir)::value;
     int o[N];
 #pragma unroll
-    for (int m = 0; m < N; ++m) o[m] = D == 0 ? o0 + m * os : D == 1 ? L::row(el, b, m) + a : L::row(el, m, b) + a;
+    for (int m = 0; m < N; ++m) o[m] = D == 0 ? L::row(el, b, a) + m : D == 1 ? L::row(el, b, m) + a : L::row(el, m, b) + a;
 #pragma unroll
     for (int f = 0; f < 5; ++f)
 #pragma unroll
@@ -223,7 +222,7 @@ k_varp_line(const DGTables tb, const DGVarpMesh mesh, int first, int count, cons
     }
     __syncthreads();
   };
-  line(std::integral_constant<int, 0>{}, L::row(el, b, a), 1);
+  line(std::integral_constant<int, 0>{});
   double2 r[UPT][5];
   // the residual: its latency overlaps the y- and z-lines
   if (MODE == 1) {
@@ -233,8 +232,8 @@ k_varp_line(const DGTables tb, const DGVarpMesh mesh, int first, int count, cons
       for (int f = 0; f < 5; ++f) r[u][f] = load_pair_nt(RR + f * T + pg[u]);
     __builtin_amdgcn_sched_barrier(0);
   }
-  line(std::integral_constant<int, 1>{}, 0, 0);
-  line(std::integral_constant<int, 2>{}, 0, 0);
+  line(std::integral_constant<int, 1>{});
+  line(std::integral_constant<int, 2>{});
 
   // ---- D: output
 #pragma unroll
