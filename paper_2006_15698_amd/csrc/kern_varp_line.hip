@@ -32,7 +32,8 @@ struct VFace {
 };
 
 // 40^3 cells, degrees 3..5, 7.8% refined (us a stage per group, k_varp before):
-// p = 3 52 (60), p = 4 271 and 85 (320, 97), p = 5 306 (392).
+// p = 3 52 (60), p = 4 252 and 85 (320, 97), p = 5 294 (392); of the last, the
+// traces for the next stage take 20.
 template <int N, int MODE, bool TR>
 __global__ void __launch_bounds__(64, 2)
 k_varp_line(const DGTables tb, const DGVarpMesh mesh, int first, int count, const double* __restrict__ Qin,

@@ -278,7 +278,7 @@ dg_varp* build(int nx, int ny, int nz, const int* refine, const int* degrees, co
   v->off[E] = T;
   v->T = T;
   // element lists by (degree, level), each in the single-degree kernel's
-  // visiting order over the cells: z-slabs of kPencilZ planes, inside a slab
+  // visiting order over the cells: z-slabs of kPencilZ planes (or one), inside a slab
   // pencils of kPencilX cells along x, inside a pencil y-row by y-row, then
   // z, x fastest; a refined cell's children together (an element's y- and
   // z-neighbours of the same group are listed close to it, so their reads
@@ -298,16 +298,35 @@ dg_varp* build(int nx, int ny, int nz, const int* refine, const int* degrees, co
     std::vector<int> fill((DG_VARP_MAXN + 1) * 2, 0);
     for (int N = 1; N <= DG_VARP_MAXN; ++N)
       for (int lev = 0; lev < 2; ++lev) fill[N * 2 + lev] = v->first[N][lev];
-    const int px = std::min(kPencilX, nx), pz = std::min(kPencilZ, nz);
-    for (int zs = 0; zs < nz; zs += pz)
+    // Where the arrays of a stage (state in and out, residual) exceed the
+    // 256 MB last-level cache, a slab is one plane and every XCD's part of the
+    // list (the launches deal it out in eighths) takes an eighth of each slab
+    // in turn: the XCDs then work on the same few planes, and the neighbours
+    // of their parts come from HBM once (us a stage: 40^3 cells of degrees 3..5,
+    // the p = 4 group 267 before, 252 so, the p = 5 group 305 and 294; 48^3
+    // p = 4 638 and 613; within the cache nothing gained, 32^3 p = 3 72 and 74).
+    const bool hbm = 15 * (int64_t)sizeof(double) * T > ((int64_t)256 << 20);
+    const int parts = hbm ? 8 : 1;
+    const int px = std::min(kPencilX, nx), pz = hbm ? 1 : std::min(kPencilZ, nz);
+    constexpr int GROUPS = (DG_VARP_MAXN + 1) * 2;
+    std::vector<int> slab[GROUPS], part[GROUPS][8];
+    for (int zs = 0; zs < nz; zs += pz) {
       for (int xs = 0; xs < nx; xs += px)
         for (int y = 0; y < ny; ++y)
           for (int z = zs; z < std::min(zs + pz, nz); ++z)
             for (int x = xs; x < std::min(xs + px, nx); ++x) {
               const int64_t c = ((int64_t)z * ny + y) * nx + x;
               for (int64_t e = cfirst[c]; e < cfirst[c + 1]; ++e)
-                v->list[fill[(v->deg[e] + 1) * 2 + v->level[e]]++] = (int)e;
+                slab[(v->deg[e] + 1) * 2 + v->level[e]].push_back((int)e);
             }
+      for (int g = 0; g < GROUPS; ++g) {
+        for (size_t i = 0; i < slab[g].size(); ++i) part[g][i * parts / slab[g].size()].push_back(slab[g][i]);
+        slab[g].clear();
+      }
+    }
+    for (int g = 0; g < GROUPS; ++g)
+      for (int x = 0; x < parts; ++x)
+        for (int e : part[g][x]) v->list[fill[g]++] = e;
   }
   // per-(degree, level) tables (the single-degree library's on the mesh of
   // that element size), Gauss-Legendre rules
