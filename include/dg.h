@@ -244,8 +244,8 @@ int dg_rk_steps(dg_ctx* ctx, double* Q, double* res, double dt, int nsteps);
 int dg_rk_steps_noalloc(dg_ctx* ctx, double* Q, double* res, double dt, int nsteps);
 
 /* As dg_rk_steps (bitwise the same result), with each step's five stage
- * launches captured once in a HIP graph (one per ping-pong parity of the
- * neighbour-read exchange) and replayed nsteps times on an internal stream
+ * launches captured once in a HIP graph (one per pair of buffers that a step
+ * reads from and ends in under the neighbour-read exchange) and replayed nsteps times on an internal stream
  * that is ordered after, and before, the context's stream by events.  The
  * graphs are kept while Q, res, dt and the context's settings stay the
  * same, and rebuilt otherwise.  Launches inside the graphs are not seen by

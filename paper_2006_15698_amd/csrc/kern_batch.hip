@@ -5,12 +5,14 @@
 //
 // A work list of (mesh, first element) items, one item per block of up to
 // EPB consecutive elements of one x-row, grouped by degree.  Each item runs
-// the same fused neighbour-read stage body as the single-mesh kernel
-// (stage_nb.h / stage_nb32.h) with the compile-time degree N and
-// elements-per-workgroup EPB of its mesh; every variant uses 256 threads.
+// the same fused neighbour-read stage body as a single-mesh kernel, with the
+// compile-time degree N and elements-per-workgroup EPB of its mesh.
 //   k_batch_degree<N, EPB>: one workgroup per item of one degree, with that
-//     variant's own registers and shared memory.
-//   k_batch_stage: a persistent grid walks the whole list (static round
+//     variant's own registers and shared memory; a wave with a thread per line
+//     (stage_line.h).
+//   k_batch_degree32<N, EPB>: the same in the FP32 form (stage_nb32.h), 256
+//     threads.
+//   k_batch_stage (stage_nb.h / stage_nb32.h, 256 threads): a persistent grid walks the whole list (static round
 //     robin: item k belongs to block k mod gridDim) through a shared-memory
 //     buffer sized for the largest variant; its register allocation is the
 //     union of all variants.
@@ -125,6 +127,16 @@ k_batch_degree32(const DGBatchInst* __restrict__ inst, const int2* __restrict__ 
                                                                 threadIdx.x);
 }
 
+// Blocks per XCD of the window of items that the XCDs share where the remap is
+// off: of 1024 at a time each takes a contiguous eighth, so that neighbours
+// along the pencils meet in its L2 while the eight stay on the same mesh.  Two
+// steps of 64 meshes of 6^3..24^3, p = 1..5: dealt out one by one 13.38 ms; 8
+// per XCD 13.50, 32 13.27, 64 13.03, 128 12.91, 256 13.02; an eighth of the whole
+// list each (the remap) 13.93.  Batches that fit the cache gain too: 16 meshes up
+// to 12^3 0.873 to 0.823, 4 meshes 0.198 to 0.189 (the last, short, window is
+// shared as well: dealt out, 0.840 and 0.195).
+constexpr int kBatchWindow = 128;
+
 // The same for FP64: the one-thread-per-line body (stage_line.h), one wave
 // per item, or per part of an item where its lines do not fit one wave
 // (N = 3: 9 elements as 5 + 4).
@@ -142,7 +154,8 @@ k_batch_degree(const DGBatchInst* __restrict__ inst, const int2* __restrict__ it
                double b, int first) {
   using BL = BatchLine<N, EPB>;
   __shared__ __align__(16) double smem[dgdev::LineSmem<N, BL::E>::size];
-  const int w = xcd ? dgdev::xcd_block(blockIdx.x, gridDim.x) : blockIdx.x;
+  const int w = xcd ? dgdev::xcd_block(blockIdx.x, gridDim.x)
+                    : dgdev::xcd_window(blockIdx.x, gridDim.x, kBatchWindow);
   const int2 it = items[begin + w / BL::PARTS];
   const int mi = __builtin_amdgcn_readfirstlane(it.x);
   const int skip = (w % BL::PARTS) * BL::E;

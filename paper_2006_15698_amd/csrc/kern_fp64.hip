@@ -4,15 +4,16 @@
 // Per RK stage one launch does the pointwise flux, the local Lax-Friedrichs
 // face flux, the sum-factorised volume contraction and lift, and the RK
 // axpy.  Two ways to obtain a neighbour's state on a shared face:
-//   k_stage_nb (stage_nb.h, the default): the neighbour's trace is
-//     interpolated from its state in the same launch; the state alternates
-//     between two buffers (Qin -> Qout).  HBM traffic per node and stage:
-//     Q and res read and written once (160 B) plus neighbour reads that
-//     miss the caches.
+//   k_stage_line (stage_line.h: a thread per line of nodes) and, for small
+//     launches and p = 0, k_stage_nb (stage_nb.h: a thread per node), the
+//     default: the neighbour's trace is interpolated from its state in the
+//     same launch; the state alternates between two buffers (Qin -> Qout).
+//     HBM traffic per node and stage: Q and res read and written once (160 B)
+//     plus neighbour reads that miss the caches.
 //   k_stage (stage_fp64.h): each launch also writes the face traces of the
 //     updated state, which the next launch reads: 160 B plus
 //     2 * 6 N^2 * 5 * 8 B per element.
-// Both give bitwise the same results.  The tree reductions below give
+// All give bitwise the same results.  The tree reductions below give
 // integrals, the maximum wave rate and the state check in a fixed order.
 
 #include "dg_internal.h"
@@ -58,7 +59,7 @@ k_stage(DGTables tb, double* __restrict__ Q, double* __restrict__ RR,
 // layout, at N = 5 (2.5% at 40^3 and 48^3); LDS-handed pairs at N = 7,
 // where they are 8% faster (at N = 4, 5, 6 and 8 they were even or 2-7%
 // slower); one point per lane at N = 3 and 8 (partner-lane pairs take
-// N = 8 past 128 registers).
+// N = 8 past 128 registers).  (Measured at sizes that lines of nodes now take.)
 template <int N>
 constexpr int kLines = N == 7 ? dgdev::LINES_LDS
                                : ((N % 2 == 0 && N <= 6) || N == 5) ? dgdev::LINES_DPP : dgdev::LINES_POINT;

@@ -10,7 +10,8 @@
 // adjoint of its own trace):
 //   1. lifted adjoint traces G_{e,+-d}(pt) = sum_m lift+-[m] gR_e(line) and
 //      forward traces T of Q, of this element and of its neighbours (read
-//      from the neighbours' Q and gR in the same launch by k_vjp_nb, or
+//      from the neighbours' Q and gR in the same launch by k_vjp_nb and, at
+//      p = 6 and 7, k_vjp_line (kern_vjp_line.hip), or
 //      exchanged through trace buffers by k_vtrace + k_vjp);
 //   2. face flux adjoint gF*_{face} = (2/h_d)(G_{plus elem,-d} - G_{minus elem,+d}),
 //      then the LF Jacobian transpose for this element's side, then the

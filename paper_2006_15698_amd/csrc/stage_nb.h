@@ -39,6 +39,15 @@ __host__ __device__ __forceinline__ int xcd_block(int w, int nblk) {
   return x * q + (x < r ? x : r) + i;
 }
 
+// The same with the XCDs sharing every 8 * per blocks (the last, short, window
+// too), each taking a contiguous eighth.
+__host__ __device__ __forceinline__ int xcd_window(int w, int nblk, int per) {
+  const int win = 8 * per, full = nblk / win * win;
+  if (w >= full) return full + xcd_block(w - full, nblk - full);
+  const int i = w % win;
+  return w - i + (i & 7) * per + (i >> 3);
+}
+
 // Elements [e0, e0 + ne), ne <= EPB, of one x-row: x0 .. x0 + ne - 1 of row
 // (y, z).
 struct Block {

@@ -3,7 +3,7 @@
 // larger ones, at n around every power of two, around multiples of d and at
 // the end of the range; and of the line kernel's LDS index (stage_line.h):
 // the nodes of a block fill their places one to one, rows whole and at even
-// places where pairs are read; and of the visiting order with shared slabs.  Exit status 0 and "ok" on success.
+// places where pairs are read; of the visiting order with shared slabs; and of the shared windows of a list.  Exit status 0 and "ok" on success.
 #include <cstdio>
 #include <vector>
 
@@ -53,7 +53,23 @@ static bool shared_slabs(int nx, int ny, int nz, int N, bool line, int pencil_z)
   return true;
 }
 
+// The windows of items that the XCDs share cover every block once.
+static bool windows(int nblk, int per) {
+  std::vector<int> hits(nblk, 0);
+  for (int w = 0; w < nblk; ++w) {
+    const int i = dgdev::xcd_window(w, nblk, per);
+    if (i < 0 || i >= nblk || hits[i]++) return false;
+  }
+  return true;
+}
+
 int main() {
+  for (int nblk : {1, 7, 8, 9, 1023, 1024, 1025, 2047, 2048, 5000, 441031})
+    for (int per : {1, 3, 128})
+      if (!windows(nblk, per)) {
+        printf("window of %d per XCD over %d blocks\n", per, nblk);
+        return 1;
+      }
   for (int nx : {1, 3, 16, 31})
     for (int ny : {1, 5, 24})
       for (int nz : {1, 2, 7, 25})
