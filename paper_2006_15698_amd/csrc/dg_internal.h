@@ -107,6 +107,7 @@ struct DGOrder {
   int share;    // blocks the XCDs share at a time: a whole slab, or all
   int full;     // whole shares
   int q;        // share / 8
+  bool hbm;     // the arrays of a stage exceed the last-level cache
   DGDiv dslab, dq, dpen, drow, dtx;   // by slab, q, and a whole pencil's blocks, blocks per y-row, blocks along x
 };
 
@@ -129,6 +130,7 @@ inline DGOrder dg_order(const dg_ctx* c, int epb, unsigned* grid, bool line = fa
   const int64_t bytes = 3 * DG_NF * (int64_t)sizeof(double) * c->E * c->N * c->N * c->N;
   const bool hbm = bytes > ((int64_t)256 << 20);
   o.xcd = c->xcd_remap;
+  o.hbm = hbm;
   o.nxb = (c->nx + epb - 1) / epb;
   const int px = pencil && c->pencil_x > 0 && c->pencil_x < c->nx ? c->pencil_x : c->nx;
   o.tx = (px + epb - 1) / epb;

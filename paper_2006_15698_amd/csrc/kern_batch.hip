@@ -170,7 +170,7 @@ k_batch_degree(const DGBatchInst* __restrict__ inst, const int2* __restrict__ it
   blk.ne = dgdev::imin(dgdev::imin(BL::E, EPB - skip), I.tab.nx - blk.x0);
   if (blk.ne <= 0) return;   // the row's last block is short
   dgdev::stage_line_body<N, MODE, BL::E>(dgdev::EulerLine<N>{{I.tab}}, I.tab, Qin + I.qoff, Qout ? Qout + I.qoff : nullptr, RR + I.qoff, a, b,
-                                         I.dt, first, blk, smem, threadIdx.x);
+                                         I.dt, first, blk, smem, threadIdx.x, false);
 }
 
 template <int N, int EPB>

@@ -93,7 +93,7 @@ template <int N> struct LineCfg { static constexpr int EPB = N == 2 ? 16 : N == 
 constexpr unsigned kLineMinWaves = 512;
 
 // Stage kernel with one thread per line, Qin -> Qout.  At 48^3 p=4 the HBM
-// stream bounds it (stages 2..5: 534 us against 632 with a thread per node;
+// stream bounds it (stages 2..5: 535 us against 632 with a thread per node;
 // reading and writing its state and residual alone takes 450): taking the
 // flux arithmetic out leaves its time as it is.
 template <int N, int MODE>
@@ -103,7 +103,8 @@ k_stage_line(DGTables tb, const double* __restrict__ Qin, double* __restrict__ Q
   constexpr int EPB = LineCfg<N>::EPB;
   __shared__ __align__(16) double smem[dgdev::LineSmem<N, EPB>::size];
   const dgdev::Block blk = dgdev::block_of<EPB>(tb, ord, blockIdx.x, gridDim.x);
-  dgdev::stage_line_body<N, MODE, EPB>(dgdev::EulerLine<N>{{tb}}, tb, Qin, Qout, RR, rka, rkb, dt, first, blk, smem, threadIdx.x);
+  dgdev::stage_line_body<N, MODE, EPB>(dgdev::EulerLine<N>{{tb}}, tb, Qin, Qout, RR, rka, rkb, dt, first, blk, smem, threadIdx.x,
+                                      N != 7 && ord.hbm);
 }
 
 // ---- reductions -----------------------------------------------------------

@@ -191,11 +191,17 @@ __device__ __forceinline__ void end_traces(const LineTables<N>& t, const double 
 // The elements of block blk, 1 <= ne <= EPB, on one wave, with the rate of the
 // volume form `form` (EulerLine; kern_split.hip has another); the other
 // arguments and MODE as for stage_nb_body.  smem: LineSmem<N, EPB>::size doubles.
+// nt: mark the new state as not reused.  Where it exceeds the last-level cache
+// the next launch finds nothing of it there, and its stores push the state the
+// neighbours read out of the L2 (48^3 p = 4 544 us a stage, marked 535; 40^3 p = 5
+// 563 / 551; 48^3 p = 3 240 / 233; 32^3 p = 7 629 / 619; 64^3 p = 2 310 / 310; only
+// 40^3 p = 6 is slower, 872 / 876); where it fits, the next launch reads it there
+// (marked, a tenth slower).
 template <int N, int MODE, int EPB, class Form>
 __device__ __forceinline__ void stage_line_body(const Form& form, const DGTables& tb, const double* __restrict__ Qin,
                                                 double* __restrict__ Qout, double* __restrict__ RR, double rka,
                                                 double rkb, double dt, int first, const Block& blk, double* smem,
-                                                int lane) {
+                                                int lane, bool nt) {
   using L = LineLds<N>;
   constexpr int N2 = N * N, N3 = N2 * N, FP = EPB * N2, SF = LineSmem<N, EPB>::SF;
   constexpr int UPT = ((EPB * N3 + 1) / 2 + 63) / 64;   // node pairs per lane and field
@@ -461,7 +467,8 @@ __device__ __forceinline__ void stage_line_body(const Form& form, const DGTables
         double2 qn;
         qn.x = fma(rkb, v.x, sS[f * SF + n]);
         qn.y = fma(rkb, v.y, sS[f * SF + n + 1]);
-        __builtin_memcpy(Qout + f * EN3 + span + g, &qn, 16);
+        if (nt) store_pair_nt(Qout + f * EN3 + span + g, qn);
+        else __builtin_memcpy(Qout + f * EN3 + span + g, &qn, 16);
         store_pair_nt(RR + f * EN3 + span + g, v);
       }
     }
