@@ -10,8 +10,8 @@
 // buffer.  A lane whose face has a flux reads a line of its own element like
 // the others, so that those loads keep their constant strides (offsets of the
 // instruction; with strides per lane 48^3 p = 4 took 646 us a stage against
-// 635, 32^3 p = 6 602 against 552) and no branch,
-// and the blocks with such a face fetch the fluxes afterwards.
+// 635, 32^3 p = 6 602 against 552) and no branch, and the blocks with such a
+// face fetch the fluxes afterwards.
 
 #include "dg_varp.h"
 #include "stage_line.h"
