@@ -92,6 +92,10 @@ __host__ __device__ __forceinline__ int dg_quot(int n, DGDiv v) {
   return (int)(((unsigned)(((unsigned long long)(unsigned)n * v.m) >> 32) + (unsigned)n) >> v.s);
 }
 
+// Elements of a wave of the one-thread-per-line kernels: as many as have their
+// N^2 lines, and their pairs of y/z neighbour points, in 64 lanes.
+constexpr int dg_line_elems(int N) { return N == 2 ? 16 : N == 3 ? 5 : N == 4 ? 4 : N == 5 ? 2 : 1; }
+
 // Order in which a neighbour-read stage launch visits its element blocks
 // (kernel argument).  A block is EPB consecutive elements of one x-row (the
 // last block of a row may be short).  Blocks are visited z-slab by z-slab

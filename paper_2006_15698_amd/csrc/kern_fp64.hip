@@ -79,10 +79,6 @@ k_stage_nb(DGTables tb, const double* __restrict__ Qin, double* __restrict__ Qou
   dgdev::stage_nb_body<N, MODE, EPB, NT, kLines<N>>(tb, Qin, Qout, RR, rka, rkb, dt, first, e0, ne, smem, threadIdx.x);
 }
 
-// One thread per line (stage_line.h): elements per wave, as many as have
-// their N^2 lines, and their pairs of y/z neighbour points, in one wave.
-template <int N> struct LineCfg { static constexpr int EPB = N == 2 ? 16 : N == 3 ? 5 : N == 4 ? 4 : N == 5 ? 2 : 1; };
-
 // Launches of up to this many waves (two per CU) go to k_stage_nb: with the
 // chip that empty a stage takes as long as one workgroup, and a wave that
 // holds whole lines runs longer than four that hold a node per thread
@@ -100,7 +96,7 @@ template <int N, int MODE>
 __global__ void __launch_bounds__(64, N == 8 ? 1 : 2)
 k_stage_line(DGTables tb, const double* __restrict__ Qin, double* __restrict__ Qout, double* __restrict__ RR,
              double rka, double rkb, double dt, int first, DGOrder ord) {
-  constexpr int EPB = LineCfg<N>::EPB;
+  constexpr int EPB = dg_line_elems(N);
   __shared__ __align__(16) double smem[dgdev::LineSmem<N, EPB>::size];
   const dgdev::Block blk = dgdev::block_of<EPB>(tb, ord, blockIdx.x, gridDim.x);
   dgdev::stage_line_body<N, MODE, EPB>(dgdev::EulerLine<N>{{tb}}, tb, Qin, Qout, RR, rka, rkb, dt, first, blk, smem, threadIdx.x,
@@ -231,7 +227,7 @@ int launch_stage_nb_n(const dg_ctx* c, const double* Qin, double* Qout, double* 
     return (int)hipGetLastError();                                                                            \
   } while (0)
   if constexpr (N >= 2) {
-    const DGOrder ord = dg_order(c, LineCfg<N>::EPB, &grid, true);
+    const DGOrder ord = dg_order(c, dg_line_elems(N), &grid, true);
     if (N == 3 || grid > kLineMinWaves) DG_LAUNCH(k_stage_line, 64);
   }
   if constexpr (N != 3) {

@@ -484,13 +484,11 @@ struct SplitLine {
   }
 };
 
-template <int N> struct SplitCfg { static constexpr int EPB = N == 2 ? 16 : N == 3 ? 5 : N == 4 ? 4 : N == 5 ? 2 : 1; };
-
 template <int N, int MODE>
 __global__ void __launch_bounds__(64, N == 8 ? 1 : N <= 3 ? 3 : 2)
 k_split_line(DGTables tb, SplitTables st, const double* __restrict__ Qin, double* __restrict__ Qout,
              double* __restrict__ RR, double a, double b, double dt, DGOrder ord) {
-  constexpr int EPB = SplitCfg<N>::EPB;
+  constexpr int EPB = dg_line_elems(N);
   __shared__ __align__(16) double smem[dgdev::LineSmem<N, EPB>::size];
   const dgdev::Block blk = dgdev::block_of<EPB>(tb, ord, blockIdx.x, gridDim.x);
   dgdev::stage_line_body<N, MODE, EPB>(SplitLine<N>{{tb}, st}, tb, Qin, Qout, RR, a, b, dt, 0, blk, smem, threadIdx.x,
@@ -520,7 +518,7 @@ int launch_split_n(const dg_ctx* c, const double* Qin, double* Qout, double* RR,
   } while (0)
   const SplitTables st = split_tables(c->tab, N);
   if constexpr (N >= 2) {
-    const DGOrder ord = dg_order(c, SplitCfg<N>::EPB, &grid, true);
+    const DGOrder ord = dg_order(c, dg_line_elems(N), &grid, true);
     if (N <= 3 || grid > kSplitLineMinWaves) DG_LAUNCH(k_split_line, 64, st);
   }
   if constexpr (N == 1 || N >= 4) {

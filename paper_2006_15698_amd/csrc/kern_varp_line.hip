@@ -19,11 +19,6 @@
 namespace dgdev {
 namespace {
 
-template <int N>
-struct VLineCfg {
-  static constexpr int EPB = N == 2 ? 16 : N == 3 ? 5 : N == 4 ? 4 : N == 5 ? 2 : 1;
-};
-
 // An entry of the face table.
 struct VFace {
   long long raw;
@@ -38,7 +33,7 @@ template <int N, int MODE, bool TR>
 __global__ void __launch_bounds__(64, 2)
 k_varp_line(const DGTables tb, const DGVarpMesh mesh, int first, int count, const double* __restrict__ Qin,
             double* __restrict__ Qout, double* __restrict__ RR, double rka, double rkb, double dt) {
-  constexpr int EPB = VLineCfg<N>::EPB;
+  constexpr int EPB = dg_line_elems(N);
   using L = LineLds<N>;
   constexpr int N2 = N * N, N3 = N2 * N, FP = EPB * N2, SF = LineSmem<N, EPB>::SF;
   constexpr int PPE = (N3 + 1) / 2;                 // node pairs of an element (the last may overlap at odd N)
@@ -309,7 +304,7 @@ constexpr int kLineMinWaves = 512;
 template <int N>
 int launch_n(hipStream_t stream, const DGTables& tb, const DGVarpMesh& m, int first, int count, const double* Qin,
              double* Qout, double* RR, int mode, double a, double b, double dt, bool tr) {
-  const dim3 grid((unsigned)((count + VLineCfg<N>::EPB - 1) / VLineCfg<N>::EPB)), blk(64);
+  const dim3 grid((unsigned)((count + dg_line_elems(N) - 1) / dg_line_elems(N))), blk(64);
 #define VARP_LAUNCH(MODE, TR) \
   hipLaunchKernelGGL((k_varp_line<N, MODE, TR>), grid, blk, 0, stream, tb, m, first, count, Qin, Qout, RR, a, b, dt)
   if (mode == 0)
@@ -334,8 +329,8 @@ bool dg_varp_line_pays(int N, int count) {
   switch (N) {
     case 2:
     case 3: return true;
-    case 4: return (count + VLineCfg<4>::EPB - 1) / VLineCfg<4>::EPB > kLineMinWaves;
-    case 5: return (count + VLineCfg<5>::EPB - 1) / VLineCfg<5>::EPB > kLineMinWaves;
+    case 4: return (count + dg_line_elems(4) - 1) / dg_line_elems(4) > kLineMinWaves;
+    case 5: return (count + dg_line_elems(5) - 1) / dg_line_elems(5) > kLineMinWaves;
     case 6:
     case 7: return count > kLineMinWaves;
     default: return false;

@@ -38,7 +38,7 @@ using dgdev::LineTables;
 
 template <int N>
 struct VLine {
-  static constexpr int EPB = N == 2 ? 16 : N == 3 ? 5 : N == 4 ? 4 : N == 5 ? 2 : 1;
+  static constexpr int EPB = dg_line_elems(N);
   static constexpr int N2 = N * N, N3 = N2 * N, FP = EPB * N2;
   static constexpr int SF = dgdev::LineSmem<N, EPB>::SF;
   static constexpr int NT = 192;
