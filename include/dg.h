@@ -152,8 +152,9 @@ int dg_set_volume_form(dg_ctx* ctx, int form);
  *   set, with DG_OPT_XCD_REMAP on, pencils are fewer planes deep where the
  *   arrays of a stage exceed the last-level cache.
  * DG_OPT_XCD_REMAP: 1 gives each of the 8 XCDs of the MI355X (each with
- *   its own L2) a contiguous part of the visiting order, or of every z-slab
- *   of PENCIL_Z planes; 0 leaves the hardware's round-robin spread of
+ *   its own L2) a contiguous part of the visiting order or, where the arrays
+ *   of a stage exceed the last-level cache, of every z-slab of PENCIL_Z
+ *   planes (of several slabs where one has few blocks); 0 leaves the hardware's round-robin spread of
  *   workgroups over the XCDs.
  * DG_OPT_VISC_FUSED: with viscosity set (FP64, standard volume form), 1
  *   forms the inviscid rate inside the viscous-flux launch from the

@@ -108,7 +108,7 @@ struct DGOrder {
   int tx;       // blocks of a pencil along x
   int tz;       // element planes of a pencil along z
   int slab;     // blocks of a whole slab
-  int share;    // blocks the XCDs share at a time: a whole slab, or all
+  int share;    // blocks the XCDs share at a time: whole slabs, or all
   int full;     // whole shares
   int q;        // share / 8
   bool hbm;     // the arrays of a stage exceed the last-level cache
@@ -116,18 +116,26 @@ struct DGOrder {
 };
 
 // Visiting order and grid size of a neighbour-read launch with EPB elements
-// per block.
+// per block; `line` for the one-thread-per-line kernels.
 //
-// Where the arrays of a stage (state in and out, residual) exceed the 256 MB
-// last-level cache the XCDs share every slab, and slabs are `planes` deep
+// Within the 256 MB last-level cache the XCDs take an eighth of the order
+// each.  Where the arrays of a stage (state in and out, residual) exceed it
+// they share every slab, and slabs are one (line kernels) or four planes deep
 // unless the caller chose a depth: the XCDs then work on the same few planes
 // and the neighbours of their parts come from HBM once.  With an eighth of
-// the whole order each, they were spread over the mesh: k_stage_line 596
-// against 557 us a stage at 48^3 p=4 (one plane; 8 planes 586), 275 against
-// 250 at 48^3 p=3; k_split 950 / 925 (4 planes) at 48^3 p=4; the viscous
-// pair 2166 / 2125; k_stage_nb32 738 / 717.  Within the cache the line kernel
-// shares slabs of 8 planes (32^3 p=3 68 us; of one plane 73), the others
-// keep an eighth of the order each (32^3 p=3 viscous 314, sharing slabs 319).
+// the whole order each, they were spread over the mesh: k_stage_line 636
+// against 534 us a stage at 48^3 p=4, 264 / 232 at 48^3 p=3, 1084 / 864 at
+// 40^3 p=6; k_split 950 / 925 (4 planes) at 48^3 p=4; the viscous pair
+// 2166 / 2125; k_stage_nb32 738 / 717.  Within the cache the eighths are as
+// fast or faster (us a stage, sharing slabs of 8 planes / eighths: 32^3 p=3
+// 66.7 / 65.2, 24^3 p=4 65.8 / 62.9, 16^3 p=5 38.7 / 37.6), by far where a slab
+// has few blocks (4x4x1024 p=3 47.5 / 34.3, 8x8x512 p=3 87.7 / 63.2).
+//
+// A plane of few blocks gives an XCD next to nothing of its own neighbours:
+// from 48 blocks down (6 per XCD) they share up to 512 blocks of whole slabs
+// (a plane / 512 blocks: 4x4x8192 p=3, 4 blocks, 354 / 265; 8x8x2048 p=3, 16
+// blocks, 313 / 268; 12x12x300 p=3, 36 blocks, 102 / 96; above, 100x2x300
+// p=3, 50 blocks, 126 / 130; 12x12x300 p=4, 72 blocks, 203 / 212).
 inline DGOrder dg_order(const dg_ctx* c, int epb, unsigned* grid, bool line = false) {
   DGOrder o;
   const bool pencil = c->order == DG_ORDER_PENCIL;
@@ -143,7 +151,9 @@ inline DGOrder dg_order(const dg_ctx* c, int epb, unsigned* grid, bool line = fa
   if (o.tz > c->nz) o.tz = c->nz;
   *grid = (unsigned)((int64_t)o.nxb * c->ny * c->nz);
   o.slab = o.nxb * c->ny * o.tz;
-  o.share = line || hbm ? o.slab : (int)*grid;
+  o.share = hbm ? o.slab : (int)*grid;
+  if (hbm && o.nxb * c->ny < 48 && o.slab < 512) o.share = o.slab * (512 / o.slab);
+  if (o.share > (int)*grid) o.share = (int)*grid;
   o.full = (int)(*grid / (unsigned)o.share);
   o.q = o.share >> 3;
   o.dslab = dg_div(o.slab);
