@@ -111,7 +111,7 @@ struct DGOrder {
   int share;    // blocks the XCDs share at a time: whole slabs, or all
   int full;     // whole shares
   int q;        // share / 8
-  bool hbm;     // the arrays of a stage exceed the last-level cache
+  bool stream;  // the new state is marked as not reused: the next launch finds little of it in the last-level cache
   DGDiv dslab, dq, dpen, drow, dtx;   // by slab, q, and a whole pencil's blocks, blocks per y-row, blocks along x
 };
 
@@ -142,7 +142,14 @@ inline DGOrder dg_order(const dg_ctx* c, int epb, unsigned* grid, bool line = fa
   const int64_t bytes = 3 * DG_NF * (int64_t)sizeof(double) * c->E * c->N * c->N * c->N;
   const bool hbm = bytes > ((int64_t)256 << 20);
   o.xcd = c->xcd_remap;
-  o.hbm = hbm;
+  // Where state in and out exceed the cache by little the next launch still
+  // finds part of the new state there: marked, 131 against 116 us a stage at
+  // 48^3 p=2 (two states 229 MiB), 128 / 113 at 30^3 p=4 (258), 120 / 117 at
+  // 38^3 p=3 (268), 148 / 145 at 22^3 p=6 (278); 161 / 159 at 52^3 p=2 and
+  // 148 / 152 at 26^3 p=5 (290); above, marked is faster: 135 / 138 at 40^3
+  // p=3 and 155 / 160 at 32^3 p=4 (313), 188 / 193 at 24^3 p=6 (362), 534 /
+  // 544 at 48^3 p=4 (1055; 40^3 p=6, 1675, even: 868 / 861).
+  o.stream = bytes / 3 * 2 > ((int64_t)300 << 20);
   o.nxb = (c->nx + epb - 1) / epb;
   const int px = pencil && c->pencil_x > 0 && c->pencil_x < c->nx ? c->pencil_x : c->nx;
   o.tx = (px + epb - 1) / epb;

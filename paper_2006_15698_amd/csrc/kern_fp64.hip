@@ -100,7 +100,7 @@ k_stage_line(DGTables tb, const double* __restrict__ Qin, double* __restrict__ Q
   __shared__ __align__(16) double smem[dgdev::LineSmem<N, EPB>::size];
   const dgdev::Block blk = dgdev::block_of<EPB>(tb, ord, blockIdx.x, gridDim.x);
   dgdev::stage_line_body<N, MODE, EPB>(dgdev::EulerLine<N>{{tb}}, tb, Qin, Qout, RR, rka, rkb, dt, first, blk, smem, threadIdx.x,
-                                      N != 7 && ord.hbm);
+                                      ord.stream);
 }
 
 // ---- reductions -----------------------------------------------------------

@@ -492,7 +492,7 @@ k_split_line(DGTables tb, SplitTables st, const double* __restrict__ Qin, double
   __shared__ __align__(16) double smem[dgdev::LineSmem<N, EPB>::size];
   const dgdev::Block blk = dgdev::block_of<EPB>(tb, ord, blockIdx.x, gridDim.x);
   dgdev::stage_line_body<N, MODE, EPB>(SplitLine<N>{{tb}, st}, tb, Qin, Qout, RR, a, b, dt, 0, blk, smem, threadIdx.x,
-                                      N != 7 && ord.hbm);
+                                      ord.stream);
 }
 
 // Launches of up to this many waves stay on k_split from N = 4: an element's

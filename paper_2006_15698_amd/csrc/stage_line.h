@@ -191,12 +191,9 @@ __device__ __forceinline__ void end_traces(const LineTables<N>& t, const double 
 // The elements of block blk, 1 <= ne <= EPB, on one wave, with the rate of the
 // volume form `form` (EulerLine; kern_split.hip has another); the other
 // arguments and MODE as for stage_nb_body.  smem: LineSmem<N, EPB>::size doubles.
-// nt: mark the new state as not reused.  Where it exceeds the last-level cache
-// the next launch finds nothing of it there, and its stores push the state the
-// neighbours read out of the L2 (48^3 p = 4 544 us a stage, marked 535; 40^3 p = 5
-// 563 / 551; 48^3 p = 3 240 / 233; 32^3 p = 7 629 / 619; 64^3 p = 2 310 / 310; only
-// 40^3 p = 6 is slower, 872 / 876); where it fits, the next launch reads it there
-// (marked, a tenth slower).
+// nt: mark the new state as not reused, for states that the next launch would
+// not find in the last-level cache anyway (DGOrder::stream): their stores then
+// do not push the state that the neighbours read out of the L2.
 template <int N, int MODE, int EPB, class Form>
 __device__ __forceinline__ void stage_line_body(const Form& form, const DGTables& tb, const double* __restrict__ Qin,
                                                 double* __restrict__ Qout, double* __restrict__ RR, double rka,

@@ -79,6 +79,20 @@ int main() {
             m.ny, m.nz, m.N, line, o.share, o.slab);
       CHECK(covers(c, o, grid, epb), "%dx%dx%d N=%d line=%d", m.nx, m.ny, m.nz, m.N, line);
     }
+  // state stores marked as not reused: only where state in and out leave
+  // nothing of the new one in the cache, at every degree alike
+  {
+    struct Case { Mesh m; bool stream; };
+    for (Case k : {Case{{36, 36, 36, 4}, false}, Case{{24, 24, 24, 6}, false}, Case{{72, 72, 72, 2}, false},
+                   Case{{48, 48, 48, 3}, false}, Case{{30, 30, 30, 5}, false}, Case{{22, 22, 22, 7}, false},
+                   Case{{40, 40, 40, 4}, true}, Case{{32, 32, 32, 5}, true}, Case{{80, 80, 80, 2}, true},
+                   Case{{48, 48, 48, 5}, true}, Case{{24, 24, 24, 7}, true}, Case{{40, 40, 40, 7}, true}}) {
+      const dg_ctx c = mesh(k.m.nx, k.m.ny, k.m.nz, k.m.N);
+      unsigned grid;
+      const DGOrder o = dg_order(&c, dg_line_elems(k.m.N), &grid, true);
+      CHECK(o.stream == k.stream, "%dx%dx%d N=%d stream %d", k.m.nx, k.m.ny, k.m.nz, k.m.N, (int)o.stream);
+    }
+  }
   // never more than the launch
   {
     dg_ctx c = mesh(1, 1, 5, 8);
