@@ -115,6 +115,13 @@ struct DGOrder {
   DGDiv dslab, dq, dpen, drow, dtx;   // by slab, q, and a whole pencil's blocks, blocks per y-row, blocks along x
 };
 
+// Bytes of the arrays that a stage streams (state in and out, residual), and
+// whether they exceed the 256 MB last-level cache.
+inline int64_t dg_stage_bytes(const dg_ctx* c) {
+  return 3 * DG_NF * (int64_t)sizeof(double) * c->E * c->N * c->N * c->N;
+}
+inline bool dg_beyond_cache(const dg_ctx* c) { return dg_stage_bytes(c) > ((int64_t)256 << 20); }
+
 // Visiting order and grid size of a neighbour-read launch with EPB elements
 // per block; `line` for the one-thread-per-line kernels.
 //
@@ -139,8 +146,7 @@ struct DGOrder {
 inline DGOrder dg_order(const dg_ctx* c, int epb, unsigned* grid, bool line = false) {
   DGOrder o;
   const bool pencil = c->order == DG_ORDER_PENCIL;
-  const int64_t bytes = 3 * DG_NF * (int64_t)sizeof(double) * c->E * c->N * c->N * c->N;
-  const bool hbm = bytes > ((int64_t)256 << 20);
+  const bool hbm = dg_beyond_cache(c);
   o.xcd = c->xcd_remap;
   // Where state in and out exceed the cache by little the next launch still
   // finds part of the new state there: marked, 131 against 116 us a stage at
@@ -149,7 +155,7 @@ inline DGOrder dg_order(const dg_ctx* c, int epb, unsigned* grid, bool line = fa
   // 148 / 152 at 26^3 p=5 (290); above, marked is faster: 135 / 138 at 40^3
   // p=3 and 155 / 160 at 32^3 p=4 (313), 188 / 193 at 24^3 p=6 (362), 534 /
   // 544 at 48^3 p=4 (1055; 40^3 p=6, 1675, even: 868 / 861).
-  o.stream = bytes / 3 * 2 > ((int64_t)300 << 20);
+  o.stream = dg_stage_bytes(c) / 3 * 2 > ((int64_t)300 << 20);
   o.nxb = (c->nx + epb - 1) / epb;
   const int px = pencil && c->pencil_x > 0 && c->pencil_x < c->nx ? c->pencil_x : c->nx;
   o.tx = (px + epb - 1) / epb;

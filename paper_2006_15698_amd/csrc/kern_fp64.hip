@@ -4,8 +4,8 @@
 // Per RK stage one launch does the pointwise flux, the local Lax-Friedrichs
 // face flux, the sum-factorised volume contraction and lift, and the RK
 // axpy.  Two ways to obtain a neighbour's state on a shared face:
-//   k_stage_line (stage_line.h: a thread per line of nodes) and, for small
-//     launches and p = 0, k_stage_nb (stage_nb.h: a thread per node), the
+//   k_stage_line (stage_line.h: a thread per line of nodes) and k_stage_nb
+//     (stage_nb.h: a thread per node), chosen by dg_stage_line_pays, the
 //     default: the neighbour's trace is interpolated from its state in the
 //     same launch; the state alternates between two buffers (Qin -> Qout).
 //     HBM traffic per node and stage: Q and res read and written once (160 B)
@@ -17,6 +17,7 @@
 // integrals, the maximum wave rate and the state check in a fixed order.
 
 #include "dg_internal.h"
+#include "line_rules.h"
 #include "stage_fp64.h"
 #include "stage_nb.h"
 #include "stage_line.h"
@@ -78,15 +79,6 @@ k_stage_nb(DGTables tb, const double* __restrict__ Qin, double* __restrict__ Qou
   dgdev::block_elements<EPB>(tb, ord, blockIdx.x, gridDim.x, e0, ne);
   dgdev::stage_nb_body<N, MODE, EPB, NT, kLines<N>>(tb, Qin, Qout, RR, rka, rkb, dt, first, e0, ne, smem, threadIdx.x);
 }
-
-// Launches of up to this many waves (two per CU) go to k_stage_nb: with the
-// chip that empty a stage takes as long as one workgroup, and a wave that
-// holds whole lines runs longer than four that hold a node per thread
-// (us per stage, k_stage_nb against k_stage_line: 8^3 p=3 7.5 / 8.8, 8^3 p=5
-// 12.7 / 13.7, 8^3 p=7 18.0 / 19.4; above, 14^3 p=3 13.1 / 12.5, 10^3 p=5
-// 15.7 / 14.3, 10^3 p=7 30.7 / 26.3).  At N = 3, where the node kernel reads
-// one point per lane, lines are faster at every size (8^3 p=2 8.1 / 7.5).
-constexpr unsigned kLineMinWaves = 512;
 
 // Stage kernel with one thread per line, Qin -> Qout.  At 48^3 p=4 the HBM
 // stream bounds it (stages 2..5: 535 us against 632 with a thread per node;
@@ -227,15 +219,14 @@ int launch_stage_nb_n(const dg_ctx* c, const double* Qin, double* Qout, double* 
     return (int)hipGetLastError();                                                                            \
   } while (0)
   if constexpr (N >= 2) {
-    const DGOrder ord = dg_order(c, dg_line_elems(N), &grid, true);
-    if (N == 3 || grid > kLineMinWaves) DG_LAUNCH(k_stage_line, 64);
+    if (dg_stage_line_pays(c)) {
+      const DGOrder ord = dg_order(c, dg_line_elems(N), &grid, true);
+      DG_LAUNCH(k_stage_line, 64);
+    }
   }
-  if constexpr (N != 3) {
-    const DGOrder ord = dg_order(c, Cfg<N>::EPB, &grid);
-    DG_LAUNCH(k_stage_nb, Cfg<N>::NT);
-  }
+  const DGOrder ord = dg_order(c, Cfg<N>::EPB, &grid);
+  DG_LAUNCH(k_stage_nb, Cfg<N>::NT);
 #undef DG_LAUNCH
-  return (int)hipErrorInvalidValue;
 }
 
 template <int N>

@@ -1,0 +1,51 @@
+// Which launches take the kernels with one thread per line (stage_line.h) and
+// which those with one thread per node.  Host code.
+//
+// A wave that holds whole lines runs longer than the waves that hold its nodes
+// one a thread, so lines need enough waves to fill the chip; and a wave of lines
+// takes up to dg_line_elems(N) elements of ONE x-row, so on short rows its
+// lanes idle where a node kernel with an element per workgroup loses nothing.
+// "waves" below are blocks of up to dg_line_elems(N) elements; all figures are
+// us a stage, lines / nodes.
+#pragma once
+
+#include "dg_internal.h"
+
+// Blocks of up to epb elements of one x-row.
+inline int64_t dg_row_blocks(const dg_ctx* c, int epb) { return (int64_t)((c->nx + epb - 1) / epb) * c->ny * c->nz; }
+
+// Whether 100 nx >= percent times the elements that the row's blocks have room for.
+inline bool dg_rows_filled(const dg_ctx* c, int epb, int percent) {
+  return 100LL * c->nx >= (int64_t)percent * ((c->nx + epb - 1) / epb) * epb;
+}
+
+// Stage of the standard form (k_stage_line / k_stage_nb).  Up to 512 waves (two
+// per CU) a stage takes as long as one workgroup: 8^3 p=3 7.5 / 6.5, 8^3 p=5
+// 12.6 / 12.0, 8^3 p=7 18.9 / 17.6; above, 14^3 p=3 11.7 / 11.8, 10^3 p=5
+// 13.9 / 15.8, 9^3 p=7 21.7 / 24.5.
+inline bool dg_stage_line_pays(const dg_ctx* c) {
+  const int N = c->N;
+  if (N < 2) return false;
+  const int64_t waves = dg_row_blocks(c, dg_line_elems(N));
+  if (N == 3) {
+    // Its node kernel reads one point per lane and is the slower at small
+    // sizes (8^3 7.5 / 8.1), but takes 9 elements a block to the lines' 5:
+    // where those fill the rows better and the arrays are in the cache the
+    // node kernel is ahead from 4096 waves on (36^3 54.2 / 51.0, 6x82x82 11%;
+    // 24^3, rows filled better by the lines, 19.7 / 22.3; beyond the cache
+    // lines 8x8x2048 167 / 173).
+    const int line = (c->nx + 4) / 5 * 5, node = (c->nx + 8) / 9 * 9;
+    return line <= node || waves <= 4096 || dg_beyond_cache(c);
+  }
+  if (waves <= 512) return false;
+  // N = 4: 2048 waves are resident at once; a second round of them ends well
+  // after the node kernel's workgroups, of which more fit (full rows in the
+  // cache: 16^3, 1024 waves, 12.2 / 13.7, 21^3 25.7 / 23.8, 24^3 32.9 / 31.4,
+  // 28^3 47.5 / 46.8, from 30^3 on 58.9 / 59.6).
+  if (N == 4 && waves > 2048 && waves <= 6144 && dg_rows_filled(c, 4, 90) && !dg_beyond_cache(c)) return false;
+  // N = 8: one wave per SIMD, 1024 at once; up to four rounds a last one that
+  // is nearly empty costs what the lines gain (10^3 24.4 / 29.6, 5x16x16
+  // 37.9 / 34.9, 13^3 5%, 16^3 95 / 96; 17x16x17 12% ahead).
+  if (N == 8 && waves > 1024 && waves <= 4096) return false;
+  return true;
+}

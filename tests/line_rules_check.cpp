@@ -1,0 +1,50 @@
+// Host check of the rules that choose between the kernels with a thread per
+// line and those with a thread per node (line_rules.h), at sizes on both sides
+// of each line.  Exit status 0 and "ok" on success.
+#include <cstdio>
+
+#include "line_rules.h"
+
+struct Case {
+  const char* form;
+  int N, nx, ny, nz;
+  bool line;
+};
+
+static dg_ctx mesh(const Case& k) {
+  dg_ctx c{};
+  c.nx = k.nx; c.ny = k.ny; c.nz = k.nz; c.N = k.N;
+  c.E = (int64_t)k.nx * k.ny * k.nz;
+  c.order = DG_ORDER_PENCIL; c.pencil_x = 16; c.pencil_z = 8; c.xcd_remap = 1;
+  return c;
+}
+
+static int fails = 0;
+template <class F>
+static void check(const char* form, F&& pays, std::initializer_list<Case> cases) {
+  for (const Case& k : cases) {
+    const dg_ctx c = mesh(k);
+    if (pays(&c) == k.line) continue;
+    ++fails;
+    printf("%s N=%d %dx%dx%d: %s expected\n", form, k.N, k.nx, k.ny, k.nz, k.line ? "lines" : "nodes");
+  }
+}
+
+int main() {
+  check("stage", dg_stage_line_pays,
+        {{"", 1, 64, 64, 64, false},
+         {"", 2, 16, 16, 32, false}, {"", 2, 16, 16, 33, true}, {"", 2, 1, 64, 64, true},
+         // 9 elements a block fill rows of 36, 27, 9, 6 better than 5 do
+         {"", 3, 36, 36, 36, false}, {"", 3, 27, 27, 27, false}, {"", 3, 6, 82, 82, false}, {"", 3, 16, 16, 128, false},
+         {"", 3, 1, 1, 1, true}, {"", 3, 8, 8, 8, true}, {"", 3, 9, 30, 30, true}, {"", 3, 28, 28, 28, true},
+         {"", 3, 40, 40, 40, true}, {"", 3, 45, 45, 45, true}, {"", 3, 8, 8, 2048, true},
+         {"", 4, 8, 16, 16, false}, {"", 4, 12, 14, 14, true}, {"", 4, 16, 16, 32, true}, {"", 4, 16, 16, 33, false},
+         {"", 4, 24, 24, 24, false}, {"", 4, 28, 28, 28, false}, {"", 4, 32, 32, 24, false}, {"", 4, 30, 30, 30, true},
+         {"", 4, 32, 32, 32, true}, {"", 4, 1, 64, 64, true}, {"", 4, 9, 37, 37, true}, {"", 4, 48, 48, 48, true},
+         {"", 5, 8, 8, 16, false}, {"", 5, 8, 8, 17, true}, {"", 6, 8, 8, 8, false}, {"", 6, 8, 8, 9, true},
+         {"", 7, 8, 8, 8, false}, {"", 7, 8, 8, 9, true},
+         {"", 8, 8, 8, 8, false}, {"", 8, 8, 8, 9, true}, {"", 8, 8, 8, 16, true}, {"", 8, 5, 16, 16, false},
+         {"", 8, 16, 16, 16, false}, {"", 8, 17, 16, 16, true}, {"", 8, 20, 20, 20, true}});
+  if (!fails) printf("ok\n");
+  return fails != 0;
+}

@@ -28,3 +28,9 @@ def test_blocks_shared_by_the_xcds(tmp_path):
     """Meshes whose planes hold few blocks (long in z) do not scatter
     neighbouring blocks over the XCDs, and every block is still visited once."""
     _run(tmp_path, "order_rules_check")
+
+
+def test_line_or_node_kernels(tmp_path):
+    """Small launches, short rows and nearly empty last rounds go to the
+    kernels with a thread per node."""
+    _run(tmp_path, "line_rules_check")
