@@ -24,7 +24,7 @@
 // instructions, which held that kernel: 48^3 p=4 927 -> 596 us a stage, 40^3
 // p=3 320 -> 160, 32^3 p=5 640 -> 361, 24^3 p=6 534 -> 245, 24^3 p=7 560 -> 323.
 //
-// k_split (p = 0 and small launches): one workgroup per element (elements
+// k_split (p = 0, small launches and short rows, dg_split_line_pays): one workgroup per element (elements
 // visited in the neighbour-read stage's order), one thread per node (the
 // pairwise fluxes make the volume term O(N^4) per element); the face points
 // of each direction on waves of their own.  The last two terms of B_f depend on
@@ -37,6 +37,7 @@
 // Qin).  MODE 2: the first stage (res = dt R without reading res).
 
 #include "dg_internal.h"
+#include "line_rules.h"
 #include "stage_fp64.h"
 #include "stage_nb.h"
 #include "stage_line.h"
@@ -495,12 +496,6 @@ k_split_line(DGTables tb, SplitTables st, const double* __restrict__ Qin, double
                                       ord.stream);
 }
 
-// Launches of up to this many waves stay on k_split from N = 4: an element's
-// whole line on one thread then runs longer than its nodes on several waves
-// (8^3 p=4 13.0 against 10.5 us a stage, 8^3 p=3 10.4 / 8.6; above, 12^3 p=3
-// 13.1 / 14.7, 12^3 p=4 17.8 / 19.0, 8^3 p=6 19.5 / 19.9).
-constexpr unsigned kSplitLineMinWaves = 384;
-
 template <int N>
 int launch_split_n(const dg_ctx* c, const double* Qin, double* Qout, double* RR, int mode, double a, double b,
                    double dt) {
@@ -518,15 +513,14 @@ int launch_split_n(const dg_ctx* c, const double* Qin, double* Qout, double* RR,
   } while (0)
   const SplitTables st = split_tables(c->tab, N);
   if constexpr (N >= 2) {
-    const DGOrder ord = dg_order(c, dg_line_elems(N), &grid, true);
-    if (N <= 3 || grid > kSplitLineMinWaves) DG_LAUNCH(k_split_line, 64, st);
+    if (dg_split_line_pays(c)) {
+      const DGOrder ord = dg_order(c, dg_line_elems(N), &grid, true);
+      DG_LAUNCH(k_split_line, 64, st);
+    }
   }
-  if constexpr (N == 1 || N >= 4) {
-    const DGOrder ord = dg_order(c, 1, &grid);
-    DG_LAUNCH(k_split, SCfg<N>::NT, st);
-  }
+  const DGOrder ord = dg_order(c, 1, &grid);
+  DG_LAUNCH(k_split, SCfg<N>::NT, st);
 #undef DG_LAUNCH
-  return (int)hipErrorInvalidValue;
 }
 
 }  // namespace

@@ -49,3 +49,25 @@ inline bool dg_stage_line_pays(const dg_ctx* c) {
   if (N == 8 && waves > 1024 && waves <= 4096) return false;
   return true;
 }
+
+// Split form (k_split_line / k_split, one element per workgroup).
+inline bool dg_split_line_pays(const dg_ctx* c) {
+  const int N = c->N, nx = c->nx;
+  if (N < 2) return false;
+  const int64_t waves = dg_row_blocks(c, dg_line_elems(N));
+  switch (N) {
+    case 2: return nx > 1 || waves <= 2048;   // 1x64x64 18.2 / 14.9, 1x16x4096 205 / 132; 1x24x24 0.71, 2x69x69 0.76
+    case 3: return nx > 1 || waves <= 512;    // 1x64x64 25.2 / 18.3, 1x39x39 18% behind, 1x24x24 even; 2x39x39 0.93
+    case 4:
+      // 9^3 10.4 / 9.3, 12x10x11 12.6 / 13.1; rows of one or two elements
+      // 1x64x64 33.1 / 24.0, 2x35x35 13% behind, 2x45x45 13% ahead; 3x20x20 even
+      return waves > 384 && nx > 1 && (nx > 2 || waves > 1536);
+    case 5:
+      // 10^3 15.4 / 13.8, 11^3 16.5 / 16.4, 12^3 17.3 / 18.4; with half-empty
+      // blocks 1x64x64 40.6 / 33.0, 3x20x20 16.2 / 14.5, 3x45x45 even
+      return waves > 704 && nx > 1 && (nx != 3 || waves > 4096);
+    case 6: return waves > 512;   // 8^3 16.6 / 14.8, 9x8x8 17.8 / 19.0
+    case 7: return waves > 384;   // 7x7x8 18.2 / 19.0 at 392
+    default: return waves > 512;  // 8^3 24.9 / 22.8, 9x8x8 26.1 / 31.5
+  }
+}

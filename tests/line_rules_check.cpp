@@ -45,6 +45,17 @@ int main() {
          {"", 7, 8, 8, 8, false}, {"", 7, 8, 8, 9, true},
          {"", 8, 8, 8, 8, false}, {"", 8, 8, 8, 9, true}, {"", 8, 8, 8, 16, true}, {"", 8, 5, 16, 16, false},
          {"", 8, 16, 16, 16, false}, {"", 8, 17, 16, 16, true}, {"", 8, 20, 20, 20, true}});
+  check("split", dg_split_line_pays,
+        {{"", 1, 64, 64, 64, false},
+         {"", 2, 1, 64, 64, false}, {"", 2, 1, 1, 4096, false}, {"", 2, 1, 24, 24, true}, {"", 2, 2, 69, 69, true},
+         {"", 2, 1, 1, 1, true}, {"", 2, 33, 5, 4, true},
+         {"", 3, 1, 64, 64, false}, {"", 3, 1, 39, 39, false}, {"", 3, 2, 39, 39, true}, {"", 3, 7, 5, 4, true},
+         {"", 4, 9, 9, 9, false}, {"", 4, 12, 12, 12, true}, {"", 4, 1, 64, 64, false}, {"", 4, 2, 35, 35, false},
+         {"", 4, 2, 48, 48, true}, {"", 4, 3, 20, 20, true}, {"", 4, 1, 16, 4096, false},
+         {"", 5, 10, 10, 10, false}, {"", 5, 12, 12, 12, true}, {"", 5, 1, 64, 64, false}, {"", 5, 3, 20, 20, false},
+         {"", 5, 3, 73, 73, true}, {"", 5, 48, 48, 48, true},
+         {"", 6, 8, 8, 8, false}, {"", 6, 9, 9, 9, true}, {"", 7, 7, 7, 7, false}, {"", 7, 7, 7, 8, true},
+         {"", 8, 8, 8, 8, false}, {"", 8, 9, 8, 8, true}});
   if (!fails) printf("ok\n");
   return fails != 0;
 }

@@ -35,3 +35,40 @@ def test_stage_node_kernels_bitwise(dgm, p, n):
     assert bool(torch.isfinite(outs[0][1]).all())
     for a, b in zip(*outs):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("p,n", [(1, (1, 49, 49)), (2, (1, 23, 23)), (3, (2, 20, 20)), (4, (3, 15, 17))])
+def test_split_node_kernels_vs_oracle(dgm, p, n):
+    """The split form on short rows: seeded elements against the oracle on the
+    3x3x3 periodic patch around each, summand-scaled 1e-12; and one step
+    against the rates of its stages."""
+    import numpy as np
+    import torch
+    from oracle import lserk
+    from oracle.splitform import SplitFormDG
+    from tests.parity import TOL, patch_rhs, split_summand_scale
+    L = (1.0, 0.8, 1.3)
+    print(f"[node split p={p} n={n}]", flush=True)
+    Q = W.random_smooth(n, p, seed=30 + p, L=L, noise=0.02)
+    s = dgm.Solver(n, p, L=L, volume_form=dgm.DG_VOLUME_KEP)
+    Qd = torch.from_numpy(Q).cuda()
+    R = s.rhs(Qd).cpu().numpy()
+    nx, ny, nz = n
+    rng = np.random.default_rng(p)
+    elems = {(0, 0, 0), (nx - 1, ny - 1, nz - 1), (nx - 1, 0, 1)}
+    elems |= {tuple(int(rng.integers(0, m)) for m in n) for _ in range(4)}
+    ref = patch_rhs(n, p, L, Q, sorted(elems), make=SplitFormDG)
+    small = SplitFormDG((3, 3, 3), p, L=tuple(3 * np.array(L) / np.array(n)))
+    for (ex, ey, ez), Ro in ref.items():
+        patch = np.ascontiguousarray(Q[:, [(ez + o) % nz for o in (-1, 0, 1)]][:, :, [(ey + o) % ny for o in (-1, 0, 1)]]
+                                     [:, :, :, [(ex + o) % nx for o in (-1, 0, 1)]])
+        scale = split_summand_scale(small, patch) + np.abs(Ro).reshape(5, -1).max(axis=1)
+        err = np.abs(R[:, ez, ey, ex] - Ro).reshape(5, -1).max(axis=1) / scale
+        assert np.all(err <= TOL), ((ex, ey, ez), err)
+    Qs, res, Qr, rr = Qd.clone(), torch.zeros_like(Qd), Qd.clone(), torch.zeros_like(Qd)
+    s.step(Qs, res, 1e-4)
+    for a, b in zip(lserk.A, lserk.B):
+        rr = a * rr + 1e-4 * s.rhs(Qr)
+        Qr = Qr + b * rr
+    torch.cuda.synchronize()
+    assert float((Qs - Qr).abs().max()) <= 1e-13 * float(Qr.abs().max())
