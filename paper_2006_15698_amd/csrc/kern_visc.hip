@@ -17,8 +17,8 @@
 // matrix divided out, as in the inviscid stage):
 //   (2/h_d) [ -sum_a Dh[i][a] X_a + l_i(+1)/w_i {X}_+ - l_i(-1)/w_i {X}_- ].
 //
-// These kernels serve p = 0 and, from p = 3, small meshes; the others run
-// those of kern_visc_line.hip.
+// These kernels serve p = 0, small meshes and short rows; the others run those
+// of kern_visc_line.hip (dg_visc_line_pays).
 //
 // Two launches per right-hand side, one workgroup per element (elements
 // visited in the neighbour-read stage's order: pencils, each XCD a
@@ -35,6 +35,7 @@
 //                launch reads another element's Q here).
 
 #include "dg_internal.h"
+#include "line_rules.h"
 #include "stage_fp64.h"
 #include "stage_nb.h"
 
@@ -594,9 +595,7 @@ int launch_visc_n(const dg_ctx* c, const double* Q, double* Fv, double* R, doubl
 
 }  // namespace
 
-// One thread per line (kern_visc_line.hip), p >= 1: whether it is the faster
-// form for this mesh, and its launches.
-bool dg_visc_line_pays(const dg_ctx* c);
+// One thread per line (kern_visc_line.hip), p >= 1.
 int dg_launch_visc_line(const dg_ctx* c, const double* Q, double* T, double* R, double* Qu, double* res, int mode,
                         double a, double b, double dt, int first, bool rate);
 
@@ -605,6 +604,8 @@ int dg_launch_visc(const dg_ctx* c, const double* Q, double* Fv, double* R, doub
   if (dg_visc_line_pays(c)) return dg_launch_visc_line(c, Q, Fv, R, Qu, res, mode, a, b, dt, first, rate);
   switch (c->N) {
     case 1: return launch_visc_n<1>(c, Q, Fv, R, Qu, res, mode, a, b, dt, first, rate);
+    case 2: return launch_visc_n<2>(c, Q, Fv, R, Qu, res, mode, a, b, dt, first, rate);
+    case 3: return launch_visc_n<3>(c, Q, Fv, R, Qu, res, mode, a, b, dt, first, rate);
     case 4: return launch_visc_n<4>(c, Q, Fv, R, Qu, res, mode, a, b, dt, first, rate);
     case 5: return launch_visc_n<5>(c, Q, Fv, R, Qu, res, mode, a, b, dt, first, rate);
     case 6: return launch_visc_n<6>(c, Q, Fv, R, Qu, res, mode, a, b, dt, first, rate);

@@ -625,37 +625,7 @@ int launch_n(const dg_ctx* c, const double* Q, double* T, double* R, double* Qu,
   return (int)hipGetLastError();
 }
 
-// Blocks of a launch from which on the line kernels are faster than those of
-// kern_visc.hip, whose node-per-thread workgroups finish sooner on a chip that
-// is not full (us per stage, kern_visc against these: 10^3 p=3 18 / 21, 12^3
-// p=3 24 / 24; 10^3 p=4 26 / 26; 16^3 p=5 112 / 114, 20^3 p=5 259 / 206; 10^3
-// p=6 68 / 55; 12^3 p=7 116 / 129, 16^3 p=7 314 / 278; at p = 1, 2 lines are
-// faster or even at every size).  At N = 6 and 8 a block's 36 or 64 lines
-// leave fewer waves on a CU (registers and LDS), so the crossover is later.
-template <int N>
-constexpr unsigned kMinBlocks = N <= 3 ? 0 : N == 6 ? 4096 : N == 8 ? 2048 : 512;
-
-template <int N>
-bool pays(const dg_ctx* c) {
-  unsigned grid;
-  (void)dg_order(c, VLine<N>::EPB, &grid, true);
-  return grid > kMinBlocks<N>;
-}
-
 }  // namespace
-
-bool dg_visc_line_pays(const dg_ctx* c) {
-  switch (c->N) {
-    case 2: return pays<2>(c);
-    case 3: return pays<3>(c);
-    case 4: return pays<4>(c);
-    case 5: return pays<5>(c);
-    case 6: return pays<6>(c);
-    case 7: return pays<7>(c);
-    case 8: return pays<8>(c);
-    default: return false;
-  }
-}
 
 int dg_launch_visc_line(const dg_ctx* c, const double* Q, double* T, double* R, double* Qu, double* res, int mode,
                         double a, double b, double dt, int first, bool rate) {

@@ -71,3 +71,32 @@ inline bool dg_split_line_pays(const dg_ctx* c) {
     default: return waves > 512;  // 8^3 24.9 / 22.8, 9x8x8 26.1 / 31.5
   }
 }
+
+// Viscous stage (k_visc_line + k_visc_update / k_visc_flux + k_visc_apply, one
+// element per workgroup).  The node pair hands a nodal flux of 12 values from
+// launch to launch; while that, the state, the rate and the residual (216
+// bytes a node) fit the cache it is close to the lines and any idle lane
+// decides, beyond it the lines gain 30 to 40%.
+inline bool dg_visc_line_pays(const dg_ctx* c) {
+  const int N = c->N, nx = c->nx;
+  if (N < 2) return false;
+  const int64_t waves = dg_row_blocks(c, dg_line_elems(N));
+  const bool cached = 216 * c->E * N * N * N <= (int64_t)256 << 20;
+  switch (N) {
+    case 2: return nx > 2 || waves <= 512;   // 1x64x64 43 / 25, 2x155x155 10% behind, 2x20x20 9% and 3x57x57 24% ahead
+    case 3: return nx > 2 || waves <= 256;   // 1x64x64 54 / 30, 2x48x48 38.3 / 35.1; 3x22x22 12% ahead
+    case 4:
+      // 12x14x14 27.8 / 27.0, 16x13x14 28.5 / 29.8; 5x49x49 17% and 6x45x45 5%
+      // behind, 17x16x16 9% ahead; beyond the cache 2x126x126 even, 5x80x80 15%
+      // ahead, 1x179x179 73% behind
+      return waves > 640 && (cached ? dg_rows_filled(c, 4, 85) : nx > 2);
+    case 5:
+      // 11x10x10 29.9 / 28.9, 10x11x12 30.7 / 32.1; 3x45x45 12%, 5x35x35 and
+      // 7x17x17 5% behind; beyond the cache 3x103x103 22% ahead, 1x126x126 6% behind
+      return waves > 600 && (cached ? dg_rows_filled(c, 2, 90) : nx > 1);
+    // a block's 36 lines leave two fifths of the lanes idle: 17^2x18 140 / 137, 18^2x19 162 / 180
+    case 6: return waves > 5632;
+    case 7: return waves > 512;    // 8x7x8 32.5 / 32.7 at 448, 9^3 44 / 48
+    default: return waves > 2816;  // 14x14x13 182 / 177, 15x14x15 225 / 235 (registers and LDS leave few waves)
+  }
+}

@@ -56,6 +56,17 @@ int main() {
          {"", 5, 3, 73, 73, true}, {"", 5, 48, 48, 48, true},
          {"", 6, 8, 8, 8, false}, {"", 6, 9, 9, 9, true}, {"", 7, 7, 7, 7, false}, {"", 7, 7, 7, 8, true},
          {"", 8, 8, 8, 8, false}, {"", 8, 9, 8, 8, true}});
+  check("viscous", dg_visc_line_pays,
+        {{"", 1, 64, 64, 64, false},
+         {"", 2, 1, 64, 64, false}, {"", 2, 2, 48, 48, false}, {"", 2, 2, 20, 20, true}, {"", 2, 3, 57, 57, true},
+         {"", 2, 1, 16, 4096, false}, {"", 2, 33, 5, 4, true},
+         {"", 3, 1, 24, 24, false}, {"", 3, 2, 48, 48, false}, {"", 3, 3, 22, 22, true}, {"", 3, 7, 5, 4, true},
+         {"", 4, 12, 14, 14, false}, {"", 4, 16, 13, 14, true}, {"", 4, 2, 48, 48, false}, {"", 4, 5, 49, 49, false},
+         {"", 4, 17, 16, 16, true}, {"", 4, 5, 80, 80, true}, {"", 4, 1, 179, 179, false}, {"", 4, 48, 48, 48, true},
+         {"", 5, 10, 11, 10, false}, {"", 5, 12, 12, 12, true}, {"", 5, 3, 45, 45, false}, {"", 5, 5, 35, 35, false},
+         {"", 5, 3, 103, 103, true}, {"", 5, 1, 126, 126, false}, {"", 5, 48, 48, 48, true},
+         {"", 6, 17, 17, 18, false}, {"", 6, 18, 18, 19, true}, {"", 6, 2, 48, 48, false},
+         {"", 7, 8, 8, 8, false}, {"", 7, 9, 8, 8, true}, {"", 8, 14, 14, 13, false}, {"", 8, 15, 14, 15, true}});
   if (!fails) printf("ok\n");
   return fails != 0;
 }

@@ -37,9 +37,11 @@ def test_stage_node_kernels_bitwise(dgm, p, n):
         assert torch.equal(a, b)
 
 
-@pytest.mark.parametrize("p,n", [(1, (1, 49, 49)), (2, (1, 23, 23)), (3, (2, 20, 20)), (4, (3, 15, 17))])
+@pytest.mark.parametrize("p,n", [(1, (1, 49, 49)), (2, (1, 23, 23)), (3, (2, 20, 20)), (4, (3, 15, 17)),
+                                 (4, (5, 13, 21))])
 def test_split_node_kernels_vs_oracle(dgm, p, n):
-    """The split form on short rows: seeded elements against the oracle on the
+    """The split form on short rows (the last mesh: lines, with a short last
+    block): seeded elements against the oracle on the
     3x3x3 periodic patch around each, summand-scaled 1e-12; and one step
     against the rates of its stages."""
     import numpy as np
@@ -72,3 +74,42 @@ def test_split_node_kernels_vs_oracle(dgm, p, n):
         Qr = Qr + b * rr
     torch.cuda.synchronize()
     assert float((Qs - Qr).abs().max()) <= 1e-13 * float(Qr.abs().max())
+
+
+@pytest.mark.parametrize("p,n", [(1, (1, 30, 30)), (2, (2, 20, 20)), (3, (17, 12, 13)), (4, (19, 9, 8)),
+                                 (5, (8, 27, 27)), (7, (5, 24, 24))])
+def test_viscous_kernels_vs_oracle(dgm, p, n):
+    """The viscous form on short rows (nodes) and, with short last blocks,
+    just above the lines' smallest launches: elements at the row ends against
+    the oracle on the 5x5x5 periodic patch around each, summand-scaled 1e-12;
+    and bitwise the same with the inviscid rate from a launch of its own."""
+    import numpy as np
+    import torch
+    from oracle.viscous import NavierStokesDG
+    from tests.parity import TOL, patch_rhs_viscous, summand_scale, visc_summand_scale
+    L, mu, pr = (1.0, 0.8, 1.3), 0.01, 0.71
+    print(f"[viscous routes p={p} n={n}]", flush=True)
+    Q = W.random_smooth(n, p, seed=10 + p, L=L, noise=0.01)
+    Qd = torch.from_numpy(Q).cuda()
+    outs = []
+    for fused in (1, 0):
+        s = dgm.Solver(n, p, L=L, mu=mu, prandtl=pr)
+        s.set_option(dgm.DG_OPT_VISC_FUSED, fused)
+        Qs, res = Qd.clone(), torch.ones_like(Qd)
+        R = s.rhs(Qd)
+        s.step(Qs, res, 1e-6, nsteps=2)
+        torch.cuda.synchronize()
+        outs.append((R, Qs, res))
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
+    R = outs[0][0].cpu().numpy()
+    nx, ny, nz = n
+    elems = [(0, 0, 0), (nx - 1, ny - 1, nz - 1), (nx // 2, 0, nz - 2)]
+    ref = patch_rhs_viscous(n, p, L, Q, elems, mu, pr)
+    small = NavierStokesDG((5, 5, 5), p, L=tuple(5 * np.array(L) / np.array(n)), mu=mu, prandtl=pr)
+    for (ex, ey, ez), Ro in ref.items():
+        xs, ys, zs = ([(e + o) % m for o in range(-2, 3)] for e, m in zip((ex, ey, ez), n))
+        patch = np.ascontiguousarray(Q[:, zs][:, :, ys][:, :, :, xs])
+        scale = summand_scale(small, patch) + visc_summand_scale(small, patch) + np.abs(Ro).reshape(5, -1).max(axis=1)
+        err = np.abs(R[:, ez, ey, ex] - Ro).reshape(5, -1).max(axis=1) / scale
+        assert np.all(err <= TOL), ((ex, ey, ez), err)
