@@ -9,7 +9,8 @@
 // compile-time degree N and elements-per-workgroup EPB of its mesh.
 //   k_batch_degree<N, EPB>: one workgroup per item of one degree, with that
 //     variant's own registers and shared memory; a wave with a thread per line
-//     (stage_line.h).
+//     (stage_line.h).  k_batch_nodes<N, EPB>, for degrees of few items: 256
+//     threads, one per node (stage_nb.h).
 //   k_batch_degree32<N, EPB>: the same in the FP32 form (stage_nb32.h), 256
 //     threads.
 //   k_batch_stage (stage_nb.h / stage_nb32.h, 256 threads): a persistent grid walks the whole list (static round
@@ -20,6 +21,7 @@
 // launch to launch; the launches of one stage read only Qin.
 
 #include "dg_batch.h"
+#include "line_rules.h"
 #include "stage_fp32.h"
 #include "stage_nb32.h"
 #include "stage_fp64.h"
@@ -173,6 +175,24 @@ k_batch_degree(const DGBatchInst* __restrict__ inst, const int2* __restrict__ it
                                          I.dt, first, blk, smem, threadIdx.x, false);
 }
 
+// The same with one thread per node (stage_nb.h), for degrees of few items.
+template <int N, int EPB, int MODE>
+__global__ void __launch_bounds__(BNT)
+k_batch_nodes(const DGBatchInst* __restrict__ inst, const int2* __restrict__ items, int begin, int xcd,
+              const double* __restrict__ Qin, double* __restrict__ Qout, double* __restrict__ RR, double a,
+              double b, int first) {
+  __shared__ double smem[smax64<N, EPB>()];
+  const int w = xcd ? dgdev::xcd_block(blockIdx.x, gridDim.x) : blockIdx.x;
+  const int2 it = items[begin + w];
+  const int mi = __builtin_amdgcn_readfirstlane(it.x);
+  const int e0 = __builtin_amdgcn_readfirstlane(it.y);
+  const DGBatchInst& I = inst[mi];
+  const int x0 = e0 % I.tab.nx;
+  const int ne = dgdev::imin(EPB, I.tab.nx - x0);
+  dgdev::stage_nb_body<N, MODE, EPB, BNT, kLines64<N>>(I.tab, Qin + I.qoff, Qout ? Qout + I.qoff : nullptr,
+                                                       RR + I.qoff, a, b, I.dt, first, e0, ne, smem, threadIdx.x);
+}
+
 template <int N, int EPB>
 void launch_degree(const DGBatchLaunch& L, int mode, const double* Qin, double* Qout, double* RR, double a, double b,
                    int first) {
@@ -184,9 +204,14 @@ void launch_degree(const DGBatchLaunch& L, int mode, const double* Qin, double* 
   if (L.f32) {
     if (mode == 0) DG_LD(k_batch_degree32, 0, 1, BNT);
     else DG_LD(k_batch_degree32, 1, 1, BNT);
-  } else {
+  } else if (dg_batch_line_pays(N, L.vcount[N])) {
     if (mode == 0) DG_LD(k_batch_degree, 0, parts, 64);
     else DG_LD(k_batch_degree, 1, parts, 64);
+  } else {
+    if constexpr (N != 3) {
+      if (mode == 0) DG_LD(k_batch_nodes, 0, 1, BNT);
+      else DG_LD(k_batch_nodes, 1, 1, BNT);
+    }
   }
 #undef DG_LD
 }

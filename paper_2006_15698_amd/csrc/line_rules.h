@@ -100,3 +100,10 @@ inline bool dg_visc_line_pays(const dg_ctx* c) {
     default: return waves > 2816;  // 14x14x13 182 / 177, 15x14x15 225 / 235 (registers and LDS leave few waves)
   }
 }
+
+// Batched stage of one degree (k_batch_degree / k_batch_nodes), N = 2..6, of
+// `items` blocks: from one per CU on (one mesh 6^3 p=3, 72 items, 9.6 / 8.9,
+// p=4 11.3 / 10.4; two 6^3 p=3, 144, 9.7 / 9.2; four 4^3 p=5, 256, even; four
+// 6^3 p=3, 288, 8% and eight 4^3 p=4, 256, 9% ahead).  At N = 3 lines are ahead at
+// every size (one 4^3 3%).
+inline bool dg_batch_line_pays(int N, int items) { return N == 3 || items >= 256; }

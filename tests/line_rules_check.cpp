@@ -67,6 +67,12 @@ int main() {
          {"", 5, 3, 103, 103, true}, {"", 5, 1, 126, 126, false}, {"", 5, 48, 48, 48, true},
          {"", 6, 17, 17, 18, false}, {"", 6, 18, 18, 19, true}, {"", 6, 2, 48, 48, false},
          {"", 7, 8, 8, 8, false}, {"", 7, 9, 8, 8, true}, {"", 8, 14, 14, 13, false}, {"", 8, 15, 14, 15, true}});
+  for (int N = 2; N <= 6; ++N)
+    for (int items : {1, 72, 255, 256, 4000})
+      if (dg_batch_line_pays(N, items) != (N == 3 || items > 255)) {
+        ++fails;
+        printf("batch N=%d items %d\n", N, items);
+      }
   if (!fails) printf("ok\n");
   return fails != 0;
 }

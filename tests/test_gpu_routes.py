@@ -113,3 +113,30 @@ def test_viscous_kernels_vs_oracle(dgm, p, n):
         scale = summand_scale(small, patch) + visc_summand_scale(small, patch) + np.abs(Ro).reshape(5, -1).max(axis=1)
         err = np.abs(R[:, ez, ey, ex] - Ro).reshape(5, -1).max(axis=1) / scale
         assert np.all(err <= TOL), ((ex, ey, ez), err)
+
+
+@pytest.mark.parametrize("p", [1, 3, 4, 5])
+def test_batch_lines_and_nodes_bitwise(dgm, p):
+    """A batch of one small mesh (a thread per node) and of forty copies of it
+    (a thread per line): the rate and two steps of every copy are the one's
+    bit for bit, as they are with every tile built for the degree."""
+    import torch
+    n = (7, 5, 3)
+    print(f"[batch routes p={p}]", flush=True)
+    q = torch.from_numpy(W.random_smooth(n, p, seed=70 + p, noise=0.02)).cuda()
+    outs = []
+    for count in (1, 40):
+        for tile in dgm.dg_batch_tile_options(p):
+            b = dgm.Batch([n] * count, [p] * count, [(1.0, 1.0, 1.0)] * count, tiles={p: tile})
+            Q = b.empty()
+            for i in range(count):
+                b.view(Q, i).copy_(q)
+            b.set_dt([1e-3] * count)
+            R, res = b.rhs(Q), torch.zeros_like(Q)
+            b.step(Q, res, nsteps=2)
+            torch.cuda.synchronize()
+            for i in (0, count // 2, count - 1):
+                outs.append([b.view(x, i).clone() for x in (R, Q, res)])
+    for o in outs[1:]:
+        for a, c in zip(outs[0], o):
+            assert torch.equal(a, c)
