@@ -85,12 +85,11 @@ struct DGVarpMesh {
 // take their flux from fbuf into m.tbuf, for the next stage's face launches.
 int dg_launch_varp(hipStream_t stream, int N, const DGTables& tb, const DGVarpMesh& m, int first, int count,
                    const double* Qin, double* Qout, double* RR, int mode, double a, double b, double dt, bool traces);
-// The same launch with one thread per line (N = 2..7), and whether a group of
-// `count` elements takes it.
+// The same launch with one thread per line (N = 2..7); line_rules.h says which
+// groups take it.
 int dg_launch_varp_line(hipStream_t stream, int N, const DGTables& tb, const DGVarpMesh& m, int first, int count,
                         const double* Qin, double* Qout, double* RR, int mode, double a, double b, double dt,
                         bool traces);
-bool dg_varp_line_pays(int N, int count);
 // The flux of the mortar faces [begin, begin + count) of Qin, all between
 // degrees lo - 1 < hi - 1 (point counts lo, hi), projected onto both sides'
 // face nodes, into m.fbuf.  from_traces: both sides' traces from m.tbuf

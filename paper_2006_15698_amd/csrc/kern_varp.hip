@@ -51,6 +51,7 @@
 // State layout: Q[f * T + off[e] + (k N + j) N + i], T the total node count.
 
 #include "dg_varp.h"
+#include "line_rules.h"
 #include "stage_nb.h"
 
 namespace dgdev {

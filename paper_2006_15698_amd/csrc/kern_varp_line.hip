@@ -292,15 +292,6 @@ k_varp_line(const DGTables tb, const DGVarpMesh mesh, int first, int count, cons
   }
 }
 
-// Groups of up to this many waves (two per CU) stay with k_varp at N = 4..7
-// (us a stage of one degree, k_varp / k_varp_line: 128 waves of N = 4 7.5 /
-// 8.9, 768 12.2 / 11.9; N = 5 256 9.9 / 10.8, 864 17.0 / 14.0; N = 6 512 12.9 /
-// 13.6, 768 14.3 / 13.7; N = 7 512 16.0 / 16.5, 768 22.1 / 20.3).  At N = 2
-// and 3 lines are faster at every size (512 elements 8.1 / 6.7 and 8.3 / 7.9),
-// at N = 8, where the lines take one wave's registers per SIMD and the
-// tables' scalar registers spill, at none (1728 elements 50.1 / 59.8).
-constexpr int kLineMinWaves = 512;
-
 template <int N>
 int launch_n(hipStream_t stream, const DGTables& tb, const DGVarpMesh& m, int first, int count, const double* Qin,
              double* Qout, double* RR, int mode, double a, double b, double dt, bool tr) {
@@ -323,19 +314,6 @@ int launch_n(hipStream_t stream, const DGTables& tb, const DGVarpMesh& m, int fi
 
 }  // namespace
 }  // namespace dgdev
-
-bool dg_varp_line_pays(int N, int count) {
-  using namespace dgdev;
-  switch (N) {
-    case 2:
-    case 3: return true;
-    case 4: return (count + dg_line_elems(4) - 1) / dg_line_elems(4) > kLineMinWaves;
-    case 5: return (count + dg_line_elems(5) - 1) / dg_line_elems(5) > kLineMinWaves;
-    case 6:
-    case 7: return count > kLineMinWaves;
-    default: return false;
-  }
-}
 
 int dg_launch_varp_line(hipStream_t stream, int N, const DGTables& tb, const DGVarpMesh& m, int first, int count,
                         const double* Qin, double* Qout, double* RR, int mode, double a, double b, double dt,

@@ -107,3 +107,19 @@ inline bool dg_visc_line_pays(const dg_ctx* c) {
 // 6^3 p=3, 288, 8% and eight 4^3 p=4, 256, 9% ahead).  At N = 3 lines are ahead at
 // every size (one 4^3 3%).
 inline bool dg_batch_line_pays(int N, int items) { return N == 3 || items >= 256; }
+
+// Variable-degree stage of one group (k_varp_line / k_varp), N = 2..7.  At N = 2
+// and 3 lines are ahead at every size (512 elements 6.7 / 8.1 and 7.9 / 8.3); at
+// N = 4..7 from two waves per CU on (128 waves of N = 4 8.7 / 7.6, 784 11.7 /
+// 12.9; N = 5 256 10.8 / 9.6, 792 12.9 / 15.7; N = 6 512 13.5 / 12.6, 900 13.5 /
+// 15.8; N = 7 448 14.7 / 15.0); at N = 8, where a wave takes a SIMD's registers
+// and the tables' scalar registers spill, at none (1728 elements 59.8 / 50.1).
+// N = 4: 1792 waves are resident at once, and a second round of a few costs more
+// than the lines gain (1805 waves 0.98, 2000 24.3 / 23.2, 2x2x2048 24.6 / 22.3,
+// 2310 even).
+inline bool dg_varp_line_pays(int N, int count) {
+  if (N < 2 || N > 7) return false;
+  if (N <= 3) return true;
+  const int epb = dg_line_elems(N), waves = (count + epb - 1) / epb;
+  return waves > 512 && !(N == 4 && waves > 1792 && waves <= 2112);
+}

@@ -73,6 +73,15 @@ int main() {
         ++fails;
         printf("batch N=%d items %d\n", N, items);
       }
+  struct Group { int N, count; bool line; };
+  for (Group g : {Group{1, 9999, false}, Group{2, 1, true}, Group{3, 1, true}, Group{4, 2048, false}, Group{4, 2049, true},
+                  Group{4, 7168, true}, Group{4, 7169, false}, Group{4, 8000, false}, Group{4, 8448, false},
+                  Group{4, 8449, true}, Group{5, 1024, false}, Group{5, 1025, true}, Group{6, 512, false},
+                  Group{6, 513, true}, Group{7, 512, false}, Group{7, 513, true}, Group{8, 9999, false}})
+    if (dg_varp_line_pays(g.N, g.count) != g.line) {
+      ++fails;
+      printf("variable degree N=%d count %d\n", g.N, g.count);
+    }
   if (!fails) printf("ok\n");
   return fails != 0;
 }

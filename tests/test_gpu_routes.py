@@ -140,3 +140,27 @@ def test_batch_lines_and_nodes_bitwise(dgm, p):
     for o in outs[1:]:
         for a, c in zip(outs[0], o):
             assert torch.equal(a, c)
+
+
+def test_variable_degree_node_round_bitwise(dgm):
+    """1800 waves of p = 3 (a thread per node) against the same mesh tiled to
+    3600 (a thread per line), bit for bit."""
+    import numpy as np
+    import torch
+    n, p = (20, 20, 18), 3
+    print("[varp node round]", flush=True)
+    q = torch.from_numpy(np.ascontiguousarray(
+        W.random_smooth(n, p, seed=3, L=(20.0, 20.0, 18.0), noise=0.02).reshape(5, n[2], n[1] * n[0] * (p + 1) ** 3))).cuda()
+    outs = []
+    for t in (1, 2):
+        m = (n[0], n[1], t * n[2])
+        v = dgm.VariableDegree(m, np.full(m[0] * m[1] * m[2], p), L=tuple(float(x) for x in m))
+        Q = q.repeat(1, t, 1).reshape(-1).contiguous()
+        res = torch.zeros_like(Q)
+        R = v.rhs(Q).clone()
+        v.step(Q, res, 1e-3, nsteps=2)
+        torch.cuda.synchronize()
+        outs.append([x.view(5, t, -1) for x in (R, Q, res)])
+    assert bool(torch.isfinite(outs[0][1]).all())
+    for a, b in zip(*outs):
+        assert torch.equal(a[:, 0], b[:, 0]) and torch.equal(a[:, 0], b[:, 1])
