@@ -11,7 +11,7 @@
 //   1. lifted adjoint traces G_{e,+-d}(pt) = sum_m lift+-[m] gR_e(line) and
 //      forward traces T of Q, of this element and of its neighbours (read
 //      from the neighbours' Q and gR in the same launch by k_vjp_nb and, at
-//      p = 6 and 7, k_vjp_line (kern_vjp_line.hip), or
+//      p = 6 and 7, k_vjp_line (kern_vjp_line.hip; dg_vjp_line_pays), or
 //      exchanged through trace buffers by k_vtrace + k_vjp);
 //   2. face flux adjoint gF*_{face} = (2/h_d)(G_{plus elem,-d} - G_{minus elem,+d}),
 //      then the LF Jacobian transpose for this element's side, then the
@@ -22,6 +22,7 @@
 // max(l-, l+) differentiates the - side when l- >= l+ (the forward's choice).
 
 #include "dg_internal.h"
+#include "line_rules.h"
 #include "stage_nb.h"
 #include "vjp_dev.h"
 
@@ -646,17 +647,14 @@ int launch_vjp_nb_n(const dg_ctx* c, const double* Q, const double* gR, double* 
 }  // namespace
 
 // One thread per line (kern_vjp_line.hip), N = 7 and 8; with gres the reverse
-// stage.  There the node kernel's LDS (95 and 139 KB an element) leaves one
-// workgroup on a CU (24^3 p=6 581 against 341 us, 24^3 p=7 1781 / 779); below
-// N = 7 it is the faster one (32^3 p=3 104 / 111, 48^3 p=4 801 / 867, 32^3 p=5
-// 583 / 657): the transposed Lax-Friedrichs Jacobians hold both, and it too
-// forms them one face point a thread.
+// stage.
 int dg_launch_vjp_line(const dg_ctx* c, const double* Q, const double* g, double* G, double* gres, double a,
                        double dt);
 
 // Neighbour reads: the product into gQ, or with gres the reverse stage.
 static int launch_vjp_neighbour(const dg_ctx* c, const double* Q, const double* gR, double* gQ, double* gres, double a,
                                 double dt) {
+  if (dg_vjp_line_pays(c)) return dg_launch_vjp_line(c, Q, gR, gQ, gres, a, dt);
   switch (c->N) {
     case 1: return launch_vjp_nb_n<1>(c, Q, gR, gQ, gres, a, dt);
     case 2: return launch_vjp_nb_n<2>(c, Q, gR, gQ, gres, a, dt);
@@ -664,8 +662,7 @@ static int launch_vjp_neighbour(const dg_ctx* c, const double* Q, const double* 
     case 4: return launch_vjp_nb_n<4>(c, Q, gR, gQ, gres, a, dt);
     case 5: return launch_vjp_nb_n<5>(c, Q, gR, gQ, gres, a, dt);
     case 6: return launch_vjp_nb_n<6>(c, Q, gR, gQ, gres, a, dt);
-    case 7:
-    case 8: return dg_launch_vjp_line(c, Q, gR, gQ, gres, a, dt);
+    case 8: return launch_vjp_nb_n<8>(c, Q, gR, gQ, gres, a, dt);
     default: return (int)hipErrorInvalidValue;
   }
 }

@@ -123,3 +123,12 @@ inline bool dg_varp_line_pays(int N, int count) {
   const int epb = dg_line_elems(N), waves = (count + epb - 1) / epb;
   return waves > 512 && !(N == 4 && waves > 1792 && waves <= 2112);
 }
+
+// Adjoint of the right-hand side (k_vjp_line / k_vjp_nb).  Below N = 7 the node
+// kernel is the faster one at every size (32^3 p=3 111 / 104, 48^3 p=4 867 / 801,
+// 32^3 p=5 657 / 583): the transposed Lax-Friedrichs Jacobians hold both, and it
+// too forms them one face point a thread.  At N = 7 and 8 its LDS (95 and 139 KB
+// an element) leaves one workgroup on a CU (24^3 p=6 341 / 581, 24^3 p=7 779 /
+// 1781); at N = 8 it is ahead while there is no more than half of one (4^3 19.1 /
+// 17.5, 5^3 19.7 / 17.6, 180 elements 22.0 / 26.3; N = 7 4^3 even).
+inline bool dg_vjp_line_pays(const dg_ctx* c) { return c->N == 7 || (c->N == 8 && c->E > 128); }

@@ -73,6 +73,9 @@ int main() {
         ++fails;
         printf("batch N=%d items %d\n", N, items);
       }
+  check("adjoint", dg_vjp_line_pays,
+        {{"", 6, 48, 48, 48, false}, {"", 7, 1, 1, 1, true}, {"", 8, 4, 4, 8, false}, {"", 8, 43, 3, 1, true},
+         {"", 8, 6, 6, 6, true}});
   struct Group { int N, count; bool line; };
   for (Group g : {Group{1, 9999, false}, Group{2, 1, true}, Group{3, 1, true}, Group{4, 2048, false}, Group{4, 2049, true},
                   Group{4, 7168, true}, Group{4, 7169, false}, Group{4, 8000, false}, Group{4, 8448, false},

@@ -164,3 +164,26 @@ def test_variable_degree_node_round_bitwise(dgm):
     assert bool(torch.isfinite(outs[0][1]).all())
     for a, b in zip(*outs):
         assert torch.equal(a[:, 0], b[:, 0]) and torch.equal(a[:, 0], b[:, 1])
+
+
+def test_adjoint_of_small_and_larger_meshes_p7(dgm):
+    """p = 7 at 128 elements (a thread per node) and at twice and 1.5 times as
+    many (lines): products and reverse stages of the default exchange against
+    the trace exchange, bit for bit."""
+    import torch
+    p = 7
+    for n in ((4, 4, 8), (3, 8, 8), (4, 8, 8)):
+        print(f"[adjoint routes n={n}]", flush=True)
+        Q = torch.from_numpy(W.random_smooth(n, p, seed=5, noise=0.02)).cuda()
+        gen = torch.Generator().manual_seed(7)
+        g0, r0 = (torch.randn(Q.shape, dtype=torch.float64, generator=gen).cuda() for _ in range(2))
+        outs = []
+        for exchange in (dgm.DG_EXCHANGE_NEIGHBOUR, dgm.DG_EXCHANGE_TRACES):
+            s = dgm.Solver(n, p)
+            s.set_option(dgm.DG_OPT_EXCHANGE, exchange)
+            gQ, gres = g0.clone(), r0.clone()
+            dgm.dg_rk_stage_vjp(s.ctx, 2, Q, gQ, gres, 1e-3)
+            outs.append((s.rhs_vjp(Q, g0), gQ, gres))
+            torch.cuda.synchronize()
+        for a, b in zip(*outs):
+            assert torch.equal(a, b)
