@@ -31,7 +31,9 @@
 namespace {
 
 using dgdev::add_line;
+using dgdev::along;
 using dgdev::Block;
+using dgdev::Dir;
 using dgdev::imin;
 using dgdev::LineLds;
 using dgdev::LineTables;
@@ -47,19 +49,6 @@ struct VLine {
   static constexpr int WORK = 14 * SF > 3 * TD ? 14 * SF : 3 * TD;
   static constexpr int size = 5 * SF + WORK;
 };
-
-template <int D>
-struct Dir {
-  static constexpr int d = D;
-};
-
-// The wave's direction as a compile-time constant (uniform over the wave).
-template <class F>
-__device__ __forceinline__ void along(int wave, F&& f) {
-  if (wave == 0) f(Dir<0>{});
-  else if (wave == 1) f(Dir<1>{});
-  else f(Dir<2>{});
-}
 
 // (u, v, w, T) of a conserved state, T = p / rho with Eq. (3)'s pressure.
 __device__ __forceinline__ void primitive(const double* q, double gm1, double* P) {

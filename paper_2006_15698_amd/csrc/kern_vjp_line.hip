@@ -2,15 +2,16 @@
 // scheme of kern_vjp.hip for N = 7 and 8, bitwise the same result; with STAGE
 // the reverse LSERK45 stage around it too.
 //
-// A workgroup of three waves owns a block of elements of one x-row, wave d
-// its lines along direction d: the neighbours' traces of Q and lifted traces
+// A workgroup of three waves owns an element, wave d its lines along direction d: the neighbours' traces of Q and lifted traces
 // of g, the transposed Lax-Friedrichs Jacobian of both ends of the line, and
 // the transposed contraction and flux Jacobian at its nodes, all in one
 // thread's registers; the three directions' parts are added in LDS in the
 // order x, y, z.  LDS per node: Q (5), g (5) and the sum (5), whose place the
 // neighbour traces had before: 41 and 61 KB an element, against 95 and 139 KB
 // for a thread per node with the x-neighbours and the face adjoints beside
-// them (24^3 p=6 581 -> 341 us, 24^3 p=7 1781 -> 779).
+// them (24^3 p=6 581 -> 341 us, 24^3 p=7 1781 -> 779).  At N = 8 the 256
+// registers a lane has with two waves on a SIMD do not hold it: 60 (product)
+// and 69 (reverse stage) are spilled, 232 and 280 bytes of scratch a lane.
 
 #include "dg_internal.h"
 #include "stage_line.h"
@@ -18,6 +19,7 @@
 
 namespace {
 
+using dgdev::along;
 using dgdev::Block;
 using dgdev::imin;
 using dgdev::LineLds;
@@ -25,25 +27,14 @@ using dgdev::LineTables;
 
 template <int N>
 struct ALine {
-  static constexpr int EPB = dg_line_elems(N);
-  static constexpr int N2 = N * N, N3 = N2 * N, FP = EPB * N2;
-  static constexpr int SF = dgdev::LineSmem<N, EPB>::SF;
+  static_assert(N >= 7 && dg_line_elems(N) == 1, "one element per workgroup");
+  static constexpr int N2 = N * N, N3 = N2 * N;
+  static constexpr int SF = dgdev::LineSmem<N, 1>::SF;
   static constexpr int NT = 192;
-  static constexpr int TD = 10 * FP;   // per direction [side][5][FP], g's traces, then Q's
+  static constexpr int TD = 10 * N2;   // per direction [side][5][N2], g's traces, then Q's
   static constexpr int WORK = 5 * SF > 3 * TD ? 5 * SF : 3 * TD;
   static constexpr int size = 10 * SF + WORK;
 };
-
-template <int D>
-struct Dir {
-  static constexpr int d = D;
-};
-template <class F>
-__device__ __forceinline__ void along(int wave, F&& f) {
-  if (wave == 0) f(Dir<0>{});
-  else if (wave == 1) f(Dir<1>{});
-  else f(Dir<2>{});
-}
 
 // Orders this wave's LDS accesses (they execute in order; the compiler must
 // keep them so).
@@ -55,19 +46,19 @@ __device__ __forceinline__ void wave_order() {
 // G = (dR/dQ)^T g, or with STAGE the reverse stage G += dt (dR/dQ)^T g in
 // place and gres = a g (g is not gres).
 template <int N, bool STAGE>
-__global__ void __launch_bounds__(192) __attribute__((amdgpu_waves_per_eu(N <= 5 ? 3 : 2, 8)))
+__global__ void __launch_bounds__(192) __attribute__((amdgpu_waves_per_eu(2, 8)))
 k_vjp_line(DGTables tb, const double* __restrict__ Q, const double* __restrict__ g, double* __restrict__ G,
            double* __restrict__ gres, double rka, double dt, DGOrder ord) {
   using V = ALine<N>;
   using L = LineLds<N>;
-  constexpr int EPB = V::EPB, N2 = V::N2, N3 = V::N3, FP = V::FP, SF = V::SF;
+  constexpr int N2 = V::N2, N3 = V::N3, SF = V::SF;
   __shared__ __align__(16) double smem[V::size];
   double* sQ = smem;              // [5][SF]
   double* sG = smem + 5 * SF;     // [5][SF]
   double* sA = smem + 10 * SF;    // [5][SF]
 
-  const Block blk = dgdev::block_of<EPB>(tb, ord, blockIdx.x, gridDim.x);
-  const int e0 = blk.e0, ne = blk.ne, nx = tb.nx, plane = tb.nx * tb.ny;
+  const Block blk = dgdev::block_of<1>(tb, ord, blockIdx.x, gridDim.x);
+  const int e0 = blk.e0, nx = tb.nx, plane = tb.nx * tb.ny;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const bool px = wave == 0;
@@ -78,9 +69,9 @@ k_vjp_line(DGTables tb, const double* __restrict__ Q, const double* __restrict__
   // ---- loads: own Q and g (node pairs over the whole workgroup), then the
   //      wave's neighbour lines (as k_visc_line), Q's and, field by field as
   //      those are used up, g's
-  constexpr int NU = (EPB * N3 + 1) / 2, PU = (5 * NU + V::NT - 1) / V::NT;
+  constexpr int NU = (N3 + 1) / 2, PU = (5 * NU + V::NT - 1) / V::NT;
   const int64_t span = (int64_t)e0 * N3;
-  const int cnt = ne * N3;
+  const int cnt = blk.ne * N3;   // N3; known to the compiler, N = 8 spills a third more registers
   double2 oq[PU], og[PU];
 #pragma unroll
   for (int u = 0; u < PU; ++u) {
@@ -89,15 +80,14 @@ k_vjp_line(DGTables tb, const double* __restrict__ Q, const double* __restrict__
     __builtin_memcpy(&oq[u], Q + p, 16);
     __builtin_memcpy(&og[u], g + p, 16);
   }
-  const dgdev::PairLane<N, EPB> pl(imin(lane, 2 * dgdev::LinePairs<N, EPB>::LPF - 1));
-  const int xside = lane >= N2;
+  const dgdev::PairLane<N, 1> pl(imin(lane, 2 * dgdev::LinePairs<N, 1>::LPF - 1));
   int64_t i0, i1 = 0;   // first nodes of the lane's neighbour lines
   int step = 1;
   if (px) {
     const int el = blk.x0 == 0 ? e0 + nx - 1 : e0 - 1;
-    const int er = blk.x0 + ne == nx ? e0 - blk.x0 : e0 + ne;
-    const int pt = imin(EPB == 1 ? lane : lane - xside * N2, N2 - 1);
-    i0 = (int64_t)(EPB > 1 && xside ? er : el) * N3 + pt * N;
+    const int er = blk.x0 + 1 == nx ? e0 - blk.x0 : e0 + 1;
+    const int pt = imin(lane, N2 - 1);
+    i0 = (int64_t)el * N3 + pt * N;
     i1 = (int64_t)er * N3 + pt * N;
   } else {
     const int ey = blk.y, ez = blk.z;
@@ -106,7 +96,7 @@ k_vjp_line(DGTables tb, const double* __restrict__ Q, const double* __restrict__
     const int ep = y ? (ey == tb.ny - 1 ? e0 - (tb.ny - 1) * nx : e0 + nx)
                      : (ez == tb.nz - 1 ? e0 - (tb.nz - 1) * plane : e0 + plane);
     step = y ? N : N2;
-    i0 = (int64_t)(pl.side ? ep : em) * N3 + imin(pl.fel, ne - 1) * N3 + (y ? dgdev::tnode<N>(1, 0, pl.pt) : pl.pt);
+    i0 = (int64_t)(pl.side ? ep : em) * N3 + (y ? dgdev::tnode<N>(1, 0, pl.pt) : pl.pt);
   }
   double2 w[5][N];
   auto load_line = [&](const double* X, int f) {
@@ -120,14 +110,12 @@ k_vjp_line(DGTables tb, const double* __restrict__ Q, const double* __restrict__
           __builtin_memcpy(&v, b0 + m, 16);
           w[f][m].x = v.x;
           w[f][m + 1 < N ? m + 1 : m].x = v.y;
-          if (EPB == 1) {   // (else the second points are not used)
-            __builtin_memcpy(&v, b1 + m, 16);
-            w[f][m].y = v.x;
-            w[f][m + 1 < N ? m + 1 : m].y = v.y;
-          }
+          __builtin_memcpy(&v, b1 + m, 16);
+          w[f][m].y = v.x;
+          w[f][m + 1 < N ? m + 1 : m].y = v.y;
         } else {
           w[f][m].x = b0[m];
-          if (EPB == 1) w[f][m].y = b1[m];
+          w[f][m].y = b1[m];
         }
       }
     } else {
@@ -148,7 +136,7 @@ k_vjp_line(DGTables tb, const double* __restrict__ Q, const double* __restrict__
     sG[n + 1] = og[u].y;
   }
   // traces of the lane's two lines (LIFT: lifted, l / w), the FMA chain of line_sum
-  const int s0 = px ? (EPB > 1 ? xside : 0) : pl.side, s1 = px ? (EPB > 1 ? xside : 1) : pl.side;
+  const int s0 = px ? 0 : pl.side, s1 = px ? 1 : pl.side;
   double q0[5], q1[5], g0[5], g1[5];
   auto trace = [&](int f, bool lift, double& t0, double& t1) {
     double v0 = 0.0, v1 = 0.0;
@@ -173,41 +161,33 @@ k_vjp_line(DGTables tb, const double* __restrict__ Q, const double* __restrict__
   // hands the lane's traces to the lines' threads
   auto give = [&](const double* t0, const double* t1) {
     if (px) {
-      if (EPB > 1) {
-        if (lane < 2 * N2) {
-          double* t = sT + (xside ? 5 * FP + (ne - 1) * N2 + lane - N2 : lane);
-#pragma unroll
-          for (int f = 0; f < 5; ++f) t[f * FP] = t0[f];
-        }
-      } else if (lane < N2) {
+      if (lane < N2) {
 #pragma unroll
         for (int f = 0; f < 5; ++f) {
-          sT[f * FP + lane] = t0[f];
-          sT[(5 + f) * FP + lane] = t1[f];
+          sT[f * N2 + lane] = t0[f];
+          sT[(5 + f) * N2 + lane] = t1[f];
         }
       }
-    } else if (lane < 2 * dgdev::LinePairs<N, EPB>::LPF) {
-      double* t = sT + pl.side * 5 * FP + pl.fel * N2 + pl.pt;
+    } else if (lane < 2 * dgdev::LinePairs<N, 1>::LPF) {
+      double* t = sT + pl.side * 5 * N2 + pl.pt;
 #pragma unroll
       for (int f = 0; f < 5; ++f) {
-        t[f * FP] = t0[f];
-        t[f * FP + 1] = t1[f];
+        t[f * N2] = t0[f];
+        t[f * N2 + 1] = t1[f];
       }
     }
   };
   give(g0, g1);
   __syncthreads();
 
-  // ---- the thread's line: line `lane` = (el, pt), pt = (a, b) tangential
-  const bool act = lane < FP;
-  const int ln = imin(lane, FP - 1);
-  const int el = ln / N2, pt = ln - el * N2;
-  const int b = pt / N, a = pt - b * N;
+  // ---- the thread's line: line `lane`, (a, b) its tangential indices
+  const bool act = lane < N2;
+  const int ln = imin(lane, N2 - 1);
+  const int b = ln / N, a = ln - b * N;
   int o[N];
 #pragma unroll
   for (int m = 0; m < N; ++m)
-    o[m] = px ? L::row(el, b, a) + m : wave == 1 ? L::row(el, b, m) + a : L::row(el, m, b) + a;
-  const bool give_r = EPB > 1 && px && act && el + 1 < ne, give_l = EPB > 1 && px && act && el > 0 && el < ne;
+    o[m] = px ? L::row(0, b, a) + m : wave == 1 ? L::row(0, b, m) + a : L::row(0, m, b) + a;
 
   // ---- end traces: the line's own, from LDS, and (after `give` and this) the
   //      neighbours' at sT[side][field][ln]
@@ -224,8 +204,6 @@ k_vjp_line(DGTables tb, const double* __restrict__ Q, const double* __restrict__
       asm volatile("" : "+v"(x), "+v"(y));
       tl[f] = x;
       tr[f] = y;
-      if (give_r) sT[f * FP + ln + N2] = y;
-      if (give_l) sT[(5 + f) * FP + ln - N2] = x;
     }
     wave_order();
   };
@@ -234,8 +212,8 @@ k_vjp_line(DGTables tb, const double* __restrict__ Q, const double* __restrict__
   own_ends(sG, true, tl, tr);
 #pragma unroll
   for (int f = 0; f < 5; ++f) {
-    fl[f] = sc * (tl[f] - sT[f * FP + ln]);
-    fr[f] = sc * (sT[(5 + f) * FP + ln] - tr[f]);
+    fl[f] = sc * (tl[f] - sT[f * N2 + ln]);
+    fr[f] = sc * (sT[(5 + f) * N2 + ln] - tr[f]);
     asm volatile("" : "+v"(fl[f]), "+v"(fr[f]));
   }
   wave_order();
@@ -251,12 +229,12 @@ k_vjp_line(DGTables tb, const double* __restrict__ Q, const double* __restrict__
     constexpr int D = decltype(dir)::d;
     double nb[5];
 #pragma unroll
-    for (int f = 0; f < 5; ++f) nb[f] = sT[f * FP + ln];
+    for (int f = 0; f < 5; ++f) nb[f] = sT[f * N2 + ln];
     dgdev::lf_vjp_d<D>(nb, tl, tb.gamma, tb.gm1, fl, false, hl);
 #pragma unroll
     for (int f = 0; f < 5; ++f) asm volatile("" : "+v"(hl[f]));
 #pragma unroll
-    for (int f = 0; f < 5; ++f) nb[f] = sT[(5 + f) * FP + ln];
+    for (int f = 0; f < 5; ++f) nb[f] = sT[(5 + f) * N2 + ln];
     dgdev::lf_vjp_d<D>(tr, nb, tb.gamma, tb.gm1, fr, true, hr);
 #pragma unroll
     for (int f = 0; f < 5; ++f) asm volatile("" : "+v"(hr[f]));
@@ -345,7 +323,7 @@ k_vjp_line(DGTables tb, const double* __restrict__ Q, const double* __restrict__
 template <int N>
 int launch_n(const dg_ctx* c, const double* Q, const double* g, double* G, double* gres, double a, double dt) {
   unsigned grid;
-  const DGOrder ord = dg_order(c, ALine<N>::EPB, &grid, true);
+  const DGOrder ord = dg_order(c, 1, &grid, true);
   if (gres)
     hipLaunchKernelGGL((k_vjp_line<N, true>), dim3(grid), dim3(192), 0, c->stream, c->tab, Q, g, G, gres, a, dt, ord);
   else

@@ -68,6 +68,19 @@ struct LineTables {
   __device__ __forceinline__ double liftp(int m) const { return tb.liftm[N - 1 - m]; }
 };
 
+// A wave's direction as a compile-time constant (uniform over the wave), where
+// the three waves of a workgroup take a direction each.
+template <int D>
+struct Dir {
+  static constexpr int d = D;
+};
+template <class F>
+__device__ __forceinline__ void along(int wave, F&& f) {
+  if (wave == 0) f(Dir<0>{});
+  else if (wave == 1) f(Dir<1>{});
+  else f(Dir<2>{});
+}
+
 template <int N, int EPB>
 struct LineSmem {
   // per-field strides are even, so that pairs stay 16-byte aligned at even N
