@@ -148,9 +148,15 @@ int dg_set_volume_form(dg_ctx* ctx, int form);
  *   (ragged pencils and rows are handled).
  * DG_OPT_PENCIL_X: elements of a pencil along x (rounded up to the
  *   kernel's block of elements; 0 = the whole row).
- * DG_OPT_PENCIL_Z: element planes of a pencil along z (>= 1).  Until it is
- *   set, with DG_OPT_XCD_REMAP on, pencils are fewer planes deep where the
- *   arrays of a stage exceed the last-level cache.
+ * DG_OPT_PENCIL_Z: element planes of a pencil along z (>= 1).  Setting it
+ *   sets DG_OPT_PENCIL_Z_AUTO to 0; reading it gives the depth that the
+ *   context's stages use, so writing back what was read leaves them as they
+ *   were.
+ * DG_OPT_PENCIL_Z_AUTO: 1 (default) leaves the depth to the library: 8
+ *   planes, but where the arrays of a stage exceed the last-level cache
+ *   (DG_ORDER_PENCIL, DG_OPT_XCD_REMAP 1) one plane in the kernels with a
+ *   thread per line and four in the others; 0 keeps the value of
+ *   DG_OPT_PENCIL_Z.
  * DG_OPT_XCD_REMAP: 1 gives each of the 8 XCDs of the MI355X (each with
  *   its own L2) a contiguous part of the visiting order or, where the arrays
  *   of a stage exceed the last-level cache, of every z-slab of PENCIL_Z
@@ -161,9 +167,9 @@ int dg_set_volume_form(dg_ctx* ctx, int form);
  *   neighbour loads that launch makes anyway; 0 gives it a launch of its
  *   own (the neighbour-read kernel).  Bitwise the same results.
  * Defaults (read back with dg_get_option): DG_EXCHANGE_NEIGHBOUR,
- * DG_ORDER_PENCIL with 16 x 8 pencils, DG_OPT_XCD_REMAP 1 and
- * DG_OPT_VISC_FUSED 1, the fastest setting measured on the Taylor-Green
- * workloads at p = 3, 4 and 6. */
+ * DG_ORDER_PENCIL with pencils of 16 elements by an automatic number of
+ * planes, DG_OPT_XCD_REMAP 1 and DG_OPT_VISC_FUSED 1, the fastest setting
+ * measured on the Taylor-Green workloads at p = 3, 4 and 6. */
 enum {
   DG_OPT_EXCHANGE = 1,
   DG_OPT_XCD_REMAP = 2,
@@ -171,7 +177,8 @@ enum {
   DG_OPT_PENCIL_X = 4,
   DG_OPT_PENCIL_Z = 5,
   DG_OPT_BATCH_LAUNCH = 6,  /* batched meshes only (dg_batch_set_option) */
-  DG_OPT_VISC_FUSED = 7
+  DG_OPT_VISC_FUSED = 7,
+  DG_OPT_PENCIL_Z_AUTO = 8
 };
 enum { DG_EXCHANGE_TRACES = 0, DG_EXCHANGE_NEIGHBOUR = 1 };
 enum { DG_ORDER_LINEAR = 0, DG_ORDER_PENCIL = 1 };

@@ -13,6 +13,7 @@
 
 #include "dg_batch.h"
 #include "dg_internal.h"
+#include "line_rules.h"
 
 namespace {
 
@@ -325,6 +326,13 @@ int stages_visc(dg_ctx* c, double* Q, double* res, double dt, int s0, int count)
   return DG_OK;
 }
 
+// Whether the context's stages run with one thread per line.
+bool stage_takes_lines(const dg_ctx* c) {
+  if (c->precision != DG_FP64) return false;
+  if (c->mu > 0.0) return dg_visc_line_pays(c);
+  return c->volume_form == DG_VOLUME_KEP ? dg_split_line_pays(c) : dg_stage_line_pays(c);
+}
+
 int stages(dg_ctx* c, double* Q, double* res, double dt, int s0, int count) {
   // Traces of the initial Q, then `count` stages starting at stage s0; each
   // stage but the last writes the traces of its updated Q for the next.
@@ -522,7 +530,7 @@ dg_ctx* dg_create(int nx, int ny, int nz, int p, double gamma) {
   c->order = DG_ORDER_PENCIL;
   c->xcd_remap = 1;
   c->pencil_x = 16;
-  c->pencil_z = 8;
+  c->pencil_z = DG_PENCIL_Z;
   c->pencil_z_set = 0;
   c->visc_fused = 1;
   c->mu = 0.0;
@@ -675,6 +683,12 @@ int dg_set_option(dg_ctx* c, int key, int value) {
     ++c->epoch;
     return DG_OK;
   }
+  if (key == DG_OPT_PENCIL_Z_AUTO) {
+    c->pencil_z_set = value ? 0 : 1;
+    if (value) c->pencil_z = DG_PENCIL_Z;
+    ++c->epoch;
+    return DG_OK;
+  }
   if (key == DG_OPT_VISC_FUSED) {
     c->visc_fused = value ? 1 : 0;
     ++c->epoch;
@@ -690,7 +704,8 @@ int dg_get_option(const dg_ctx* c, int key, int* value) {
     case DG_OPT_XCD_REMAP: *value = c->xcd_remap; return DG_OK;
     case DG_OPT_ORDER: *value = c->order; return DG_OK;
     case DG_OPT_PENCIL_X: *value = c->pencil_x; return DG_OK;
-    case DG_OPT_PENCIL_Z: *value = c->pencil_z; return DG_OK;
+    case DG_OPT_PENCIL_Z: *value = dg_pencil_depth(c, stage_takes_lines(c)); return DG_OK;
+    case DG_OPT_PENCIL_Z_AUTO: *value = !c->pencil_z_set; return DG_OK;
     case DG_OPT_VISC_FUSED: *value = c->visc_fused; return DG_OK;
     default: return fail(DG_EINVAL, "unknown option %d", key);
   }

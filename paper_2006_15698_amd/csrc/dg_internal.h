@@ -54,7 +54,7 @@ struct dg_ctx {
   int order;      // DG_ORDER_LINEAR or DG_ORDER_PENCIL
   int pencil_x;   // pencil extent along x in elements (0: whole row)
   int pencil_z;   // pencil extent along z in element planes
-  int pencil_z_set;  // pencil_z was chosen by the caller (dg_order)
+  int pencil_z_set;  // pencil_z was chosen by the caller (DG_OPT_PENCIL_Z_AUTO 0)
   int visc_fused; // viscous FP64 standard form: inviscid rate inside the viscous-flux launch
   // viscous terms (dg_set_viscosity): dynamic viscosity, Prandtl number and
   // conductivity mu gamma / ((gamma - 1) Pr); mu = 0 is the Euler equations
@@ -122,6 +122,14 @@ inline int64_t dg_stage_bytes(const dg_ctx* c) {
 }
 inline bool dg_beyond_cache(const dg_ctx* c) { return dg_stage_bytes(c) > ((int64_t)256 << 20); }
 
+#define DG_PENCIL_Z 8   // planes of a pencil unless the caller chose
+
+// Planes of a pencil in a launch of c (before the mesh's own height).
+inline int dg_pencil_depth(const dg_ctx* c, bool line) {
+  const bool chosen = c->pencil_z_set || c->order != DG_ORDER_PENCIL || !c->xcd_remap || !dg_beyond_cache(c);
+  return chosen ? c->pencil_z : line ? 1 : 4;
+}
+
 // Visiting order and grid size of a neighbour-read launch with EPB elements
 // per block; `line` for the one-thread-per-line kernels.
 //
@@ -159,8 +167,7 @@ inline DGOrder dg_order(const dg_ctx* c, int epb, unsigned* grid, bool line = fa
   o.nxb = (c->nx + epb - 1) / epb;
   const int px = pencil && c->pencil_x > 0 && c->pencil_x < c->nx ? c->pencil_x : c->nx;
   o.tx = (px + epb - 1) / epb;
-  o.tz = !pencil || c->pencil_z < 1 ? 1 : c->pencil_z;
-  if (pencil && o.xcd && hbm && !c->pencil_z_set) o.tz = line ? 1 : 4;
+  o.tz = !pencil || c->pencil_z < 1 ? 1 : dg_pencil_depth(c, line);
   if (o.tz > c->nz) o.tz = c->nz;
   *grid = (unsigned)((int64_t)o.nxb * c->ny * c->nz);
   o.slab = o.nxb * c->ny * o.tz;

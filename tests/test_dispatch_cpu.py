@@ -34,3 +34,30 @@ def test_line_or_node_kernels(tmp_path):
     """Small launches, short rows and nearly empty last rounds go to the
     kernels with a thread per node."""
     _run(tmp_path, "line_rules_check")
+
+
+def test_pencil_depth_option_round_trips():
+    """DG_OPT_PENCIL_Z reads as the depth that the stages use; writing back
+    what was read keeps it, and DG_OPT_PENCIL_Z_AUTO goes back to automatic."""
+    from paper_2006_15698_amd import dg
+    for n, p, prec, depth in ((48, 4, dg.DG_FP64, 1), (48, 4, dg.DG_FP32_MFMA, 4), (32, 3, dg.DG_FP64, 8),
+                              (96, 0, dg.DG_FP64, 8), (160, 0, dg.DG_FP64, 4)):
+        ctx = dg.dg_create(n, n, n, p, 1.4)
+        try:
+            dg.dg_set_precision(ctx, prec)
+            read = lambda: (dg.dg_get_option(ctx, dg.DG_OPT_PENCIL_Z), dg.dg_get_option(ctx, dg.DG_OPT_PENCIL_Z_AUTO))
+            assert read() == (depth, 1)
+            before = {k: dg.dg_get_option(ctx, k) for k in dg.OPTION_NAMES}
+            for k, v in before.items():
+                dg.dg_set_option(ctx, k, v)
+            assert {k: dg.dg_get_option(ctx, k) for k in dg.OPTION_NAMES} == before
+            dg.dg_set_option(ctx, dg.DG_OPT_PENCIL_Z, depth)
+            assert read() == (depth, 0)
+            dg.dg_set_option(ctx, dg.DG_OPT_PENCIL_Z, 3)
+            assert read() == (3, 0)
+            dg.dg_set_option(ctx, dg.DG_OPT_PENCIL_Z_AUTO, 1)
+            assert read() == (depth, 1)
+            dg.dg_set_option(ctx, dg.DG_OPT_XCD_REMAP, 0)
+            assert read() == (8, 1)
+        finally:
+            dg.dg_destroy(ctx)
