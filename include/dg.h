@@ -178,7 +178,8 @@ enum {
   DG_OPT_PENCIL_Z = 5,
   DG_OPT_BATCH_LAUNCH = 6,  /* batched meshes only (dg_batch_set_option) */
   DG_OPT_VISC_FUSED = 7,
-  DG_OPT_PENCIL_Z_AUTO = 8
+  DG_OPT_PENCIL_Z_AUTO = 8,
+  DG_OPT_XCD_WINDOW = 9     /* batched meshes only (dg_batch_set_option) */
 };
 enum { DG_EXCHANGE_TRACES = 0, DG_EXCHANGE_NEIGHBOUR = 1 };
 enum { DG_ORDER_LINEAR = 0, DG_ORDER_PENCIL = 1 };
@@ -350,7 +351,10 @@ int dg_batch_set_tile(dg_batch* b, int p, int epb);
  *   parts of equal node count and XCD x gets part x of each group, so that
  *   every XCD runs the same mix of degrees.  Either way the items that run
  *   at the same time on one XCD are neighbours in the list and share its
- *   L2; 0 (default) leaves the round-robin spread of workgroups.
+ *   L2; 0 (default) leaves the spread to DG_OPT_XCD_WINDOW.
+ * DG_OPT_XCD_WINDOW 1 (default): with DG_OPT_XCD_REMAP 0 and one launch per
+ *   degree, the XCDs share 1024 items at a time, each taking a contiguous
+ *   eighth; 0 leaves the round-robin spread of workgroups.
  * DG_OPT_ORDER: items of a mesh row by row (DG_ORDER_LINEAR) or in
  *   pencils of DG_OPT_PENCIL_X elements (0 = the whole row) by
  *   DG_OPT_PENCIL_Z planes swept along y (DG_ORDER_PENCIL, default, 16 x 8),

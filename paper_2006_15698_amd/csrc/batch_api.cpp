@@ -39,9 +39,10 @@ struct dg_batch {
   // launch form and visiting order of the work list (dg_batch_set_option).
   // Defaults: the fastest measured on the 512-mesh workload: one launch per
   // degree (20.1 against 14.5 GDOF-stages/s for the persistent launch in
-  // FP64, 16.9 against 11.4 in the FP32 form), pencil order; the XCD remap
-  // and the order move the per-degree rates by under 2%
+  // FP64, 16.9 against 11.4 in the FP32 form), pencil order, windows of items
+  // shared by the XCDs (DG_BATCH_WINDOW)
   int xcd = 0;                 // each XCD walks its own contiguous part of the list
+  int window = 1;              // windows of items shared by the XCDs (FP64, one launch per degree, xcd 0)
   int order = DG_ORDER_PENCIL; // item order within a mesh
   int pencil_x = 16;           // elements of a pencil along x (0 = whole row)
   int pencil_z = 8;            // element planes of a pencil along z
@@ -158,7 +159,7 @@ DGBatchLaunch launch_of(const dg_batch* b, hipStream_t s) {
   l.stream = s;
   l.split = b->split;
   l.per_degree = b->launch == DG_BATCH_PER_DEGREE;
-  l.xcd = b->xcd;
+  l.deal = b->xcd ? DG_DEAL_PARTS : b->window ? DG_DEAL_WINDOWS : DG_DEAL_PLAIN;
   for (int N = 0; N <= DG_MAXN; ++N) {
     l.vbegin[N] = b->vbegin[N];
     l.vcount[N] = b->vcount[N];
@@ -312,6 +313,7 @@ int dg_batch_set_option(dg_batch* b, int key, int value) {
   if (!b) return dg_set_error(DG_EINVAL, "NULL batch");
   switch (key) {
     case DG_OPT_XCD_REMAP: b->xcd = value ? 1 : 0; break;
+    case DG_OPT_XCD_WINDOW: b->window = value ? 1 : 0; break;
     case DG_OPT_ORDER:
       if (value != DG_ORDER_LINEAR && value != DG_ORDER_PENCIL) return dg_set_error(DG_EINVAL, "unknown order %d", value);
       b->order = value;
@@ -349,6 +351,7 @@ int dg_batch_get_option(const dg_batch* b, int key, int* value) {
   if (!b || !value) return dg_set_error(DG_EINVAL, "NULL argument");
   switch (key) {
     case DG_OPT_XCD_REMAP: *value = b->xcd; return DG_OK;
+    case DG_OPT_XCD_WINDOW: *value = b->window; return DG_OK;
     case DG_OPT_BATCH_LAUNCH: *value = b->launch; return DG_OK;
     case DG_OPT_ORDER: *value = b->order; return DG_OK;
     case DG_OPT_PENCIL_X: *value = b->pencil_x; return DG_OK;

@@ -24,6 +24,22 @@ struct DGBatchSplit {
   int bounds[9];
 };
 
+// How a launch of one degree deals its items to the XCDs.
+enum {
+  DG_DEAL_PLAIN = 0,     // item w to workgroup w: round robin
+  DG_DEAL_PARTS = 1,     // a contiguous eighth of the items each
+  DG_DEAL_WINDOWS = 2    // a contiguous eighth of every DG_BATCH_WINDOW * 8 items (xcd_window)
+};
+
+// Items per XCD of a window, a power of two.  Two steps of 64 meshes of
+// 6^3..24^3, p = 1..5: dealt out one by one 13.38 ms; 8 per XCD 13.50, 32 13.27,
+// 64 13.03, 128 12.91, 256 13.02; an eighth of the whole list each 13.93.
+// Neighbours along the pencils meet in an XCD's L2 while the eight stay on the
+// same mesh.  Batches that fit the cache gain too: 16 meshes up to 12^3 0.873 to
+// 0.823, 4 meshes 0.198 to 0.189 (the last, short, window is shared as well:
+// dealt out, 0.840 and 0.195).
+#define DG_BATCH_WINDOW 128
+
 struct DGBatchLaunch {
   const DGBatchInst* inst;
   const int2* items;  // (mesh, first element)
@@ -33,10 +49,10 @@ struct DGBatchLaunch {
   int f32;
   DGBatchSplit split;
   // one launch per degree (DG_BATCH_PER_DEGREE): the items of point count N
-  // are items[vbegin[N] .. vbegin[N] + vcount[N]), all with tile epb[N];
-  // xcd: each XCD takes a contiguous part of them
+  // are items[vbegin[N] .. vbegin[N] + vcount[N]), all with tile epb[N],
+  // dealt to the XCDs by `deal`
   int per_degree;
-  int xcd;
+  int deal;
   int vbegin[DG_MAXN + 1], vcount[DG_MAXN + 1], epb[DG_MAXN + 1];
 };
 

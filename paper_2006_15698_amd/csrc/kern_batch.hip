@@ -107,17 +107,22 @@ k_batch_stage(const DGBatchInst* __restrict__ inst, const int2* __restrict__ ite
   }
 }
 
+// This workgroup's place among the launch's items (DG_DEAL_*).
+__device__ __forceinline__ int deal_item(int deal) {
+  const int w = blockIdx.x, n = gridDim.x;
+  return deal == DG_DEAL_WINDOWS ? dgdev::xcd_window(w, n, DG_BATCH_WINDOW) : deal == DG_DEAL_PARTS ? dgdev::xcd_block(w, n) : w;
+}
+
 // One (N, EPB) variant over its own items, one workgroup per item
 // (DG_BATCH_PER_DEGREE), FP32 contractions: the variant's own register
-// allocation and shared memory.  With xcd set, workgroup w takes item
-// xcd_block(w): each XCD a contiguous part of the items.
+// allocation and shared memory.
 template <int N, int EPB, int MODE>
 __global__ void __launch_bounds__(BNT)
-k_batch_degree32(const DGBatchInst* __restrict__ inst, const int2* __restrict__ items, int begin, int xcd,
+k_batch_degree32(const DGBatchInst* __restrict__ inst, const int2* __restrict__ items, int begin, int deal,
                  const double* __restrict__ Qin, double* __restrict__ Qout, double* __restrict__ RR, double a,
                  double b, int first) {
   __shared__ double smem[(smax32<N, EPB>() + 7) / 8];
-  const int w = xcd ? dgdev::xcd_block(blockIdx.x, gridDim.x) : blockIdx.x;
+  const int w = deal_item(deal);
   const int2 it = items[begin + w];
   const int mi = __builtin_amdgcn_readfirstlane(it.x);
   const int e0 = __builtin_amdgcn_readfirstlane(it.y);
@@ -128,16 +133,6 @@ k_batch_degree32(const DGBatchInst* __restrict__ inst, const int2* __restrict__ 
                                                                 RR + I.qoff, a, b, I.dt, first, e0, ne, smem,
                                                                 threadIdx.x);
 }
-
-// Blocks per XCD of the window of items that the XCDs share where the remap is
-// off: of 1024 at a time each takes a contiguous eighth, so that neighbours
-// along the pencils meet in its L2 while the eight stay on the same mesh.  Two
-// steps of 64 meshes of 6^3..24^3, p = 1..5: dealt out one by one 13.38 ms; 8
-// per XCD 13.50, 32 13.27, 64 13.03, 128 12.91, 256 13.02; an eighth of the whole
-// list each (the remap) 13.93.  Batches that fit the cache gain too: 16 meshes up
-// to 12^3 0.873 to 0.823, 4 meshes 0.198 to 0.189 (the last, short, window is
-// shared as well: dealt out, 0.840 and 0.195).
-constexpr int kBatchWindow = 128;
 
 // The same for FP64: the one-thread-per-line body (stage_line.h), one wave
 // per item, or per part of an item where its lines do not fit one wave
@@ -151,13 +146,12 @@ struct BatchLine {
 
 template <int N, int EPB, int MODE>
 __global__ void __launch_bounds__(64, 2)
-k_batch_degree(const DGBatchInst* __restrict__ inst, const int2* __restrict__ items, int begin, int xcd,
+k_batch_degree(const DGBatchInst* __restrict__ inst, const int2* __restrict__ items, int begin, int deal,
                const double* __restrict__ Qin, double* __restrict__ Qout, double* __restrict__ RR, double a,
                double b, int first) {
   using BL = BatchLine<N, EPB>;
   __shared__ __align__(16) double smem[dgdev::LineSmem<N, BL::E>::size];
-  const int w = xcd ? dgdev::xcd_block(blockIdx.x, gridDim.x)
-                    : dgdev::xcd_window(blockIdx.x, gridDim.x, kBatchWindow);
+  const int w = deal_item(deal);
   const int2 it = items[begin + w / BL::PARTS];
   const int mi = __builtin_amdgcn_readfirstlane(it.x);
   const int skip = (w % BL::PARTS) * BL::E;
@@ -178,11 +172,11 @@ k_batch_degree(const DGBatchInst* __restrict__ inst, const int2* __restrict__ it
 // The same with one thread per node (stage_nb.h), for degrees of few items.
 template <int N, int EPB, int MODE>
 __global__ void __launch_bounds__(BNT)
-k_batch_nodes(const DGBatchInst* __restrict__ inst, const int2* __restrict__ items, int begin, int xcd,
+k_batch_nodes(const DGBatchInst* __restrict__ inst, const int2* __restrict__ items, int begin, int deal,
               const double* __restrict__ Qin, double* __restrict__ Qout, double* __restrict__ RR, double a,
               double b, int first) {
   __shared__ double smem[smax64<N, EPB>()];
-  const int w = xcd ? dgdev::xcd_block(blockIdx.x, gridDim.x) : blockIdx.x;
+  const int w = deal_item(deal);
   const int2 it = items[begin + w];
   const int mi = __builtin_amdgcn_readfirstlane(it.x);
   const int e0 = __builtin_amdgcn_readfirstlane(it.y);
@@ -199,7 +193,7 @@ void launch_degree(const DGBatchLaunch& L, int mode, const double* Qin, double* 
   const int begin = L.vbegin[N];
 #define DG_LD(kernel, m, parts, threads)                                                                            \
   hipLaunchKernelGGL((kernel<N, EPB, m>), dim3((unsigned)(L.vcount[N] * (parts))), dim3(threads), 0, L.stream, L.inst, \
-                     L.items, begin, L.xcd, Qin, Qout, RR, a, b, first)
+                     L.items, begin, L.deal, Qin, Qout, RR, a, b, first)
   constexpr int parts = BatchLine<N, EPB>::PARTS;
   if (L.f32) {
     if (mode == 0) DG_LD(k_batch_degree32, 0, 1, BNT);

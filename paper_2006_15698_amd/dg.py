@@ -50,13 +50,14 @@ DG_ORDER_PENCIL = 1
 DG_OPT_BATCH_LAUNCH = 6
 DG_OPT_VISC_FUSED = 7
 DG_OPT_PENCIL_Z_AUTO = 8
+DG_OPT_XCD_WINDOW = 9
 DG_BATCH_PERSISTENT = 0
 DG_BATCH_PER_DEGREE = 1
 OPTION_NAMES = {DG_OPT_EXCHANGE: "exchange", DG_OPT_XCD_REMAP: "xcd_remap", DG_OPT_ORDER: "order",
                 DG_OPT_PENCIL_X: "pencil_x", DG_OPT_PENCIL_Z: "pencil_z", DG_OPT_PENCIL_Z_AUTO: "pencil_z_auto",
                 DG_OPT_VISC_FUSED: "visc_fused"}
 BATCH_OPTION_NAMES = {DG_OPT_XCD_REMAP: "xcd_remap", DG_OPT_ORDER: "order", DG_OPT_PENCIL_X: "pencil_x",
-                      DG_OPT_PENCIL_Z: "pencil_z", DG_OPT_BATCH_LAUNCH: "batch_launch"}
+                      DG_OPT_PENCIL_Z: "pencil_z", DG_OPT_BATCH_LAUNCH: "batch_launch", DG_OPT_XCD_WINDOW: "xcd_window"}
 
 ERROR_NAMES = {DG_EINVAL: "DG_EINVAL", DG_EUNSUPPORTED: "DG_EUNSUPPORTED", DG_EHIP: "DG_EHIP",
                DG_EALIAS: "DG_EALIAS", DG_ENONPHYSICAL: "DG_ENONPHYSICAL",
@@ -474,7 +475,7 @@ class Batch:
 
     def set_option(self, key, value):
         """Work-list visiting order (DG_OPT_XCD_REMAP, DG_OPT_ORDER,
-        DG_OPT_PENCIL_X, DG_OPT_PENCIL_Z) and launch form
+        DG_OPT_XCD_WINDOW, DG_OPT_PENCIL_X, DG_OPT_PENCIL_Z) and launch form
         (DG_OPT_BATCH_LAUNCH); results are bitwise unchanged."""
         self._s()
         dg_batch_set_option(self.b, key, value)

@@ -61,3 +61,24 @@ def test_pencil_depth_option_round_trips():
             assert read() == (8, 1)
         finally:
             dg.dg_destroy(ctx)
+
+
+def test_batch_window_option():
+    """Every deal of a batch's items can be had and read back."""
+    from paper_2006_15698_amd import dg
+    b = dg.dg_batch_create([(4, 4, 4)], [3], [(1.0, 1.0, 1.0)])
+    try:
+        read = lambda: (dg.dg_batch_get_option(b, dg.DG_OPT_XCD_REMAP), dg.dg_batch_get_option(b, dg.DG_OPT_XCD_WINDOW))
+        assert read() == (0, 1)
+        for xcd, window in ((0, 0), (1, 0), (1, 1), (0, 1)):
+            dg.dg_batch_set_option(b, dg.DG_OPT_XCD_REMAP, xcd)
+            dg.dg_batch_set_option(b, dg.DG_OPT_XCD_WINDOW, window)
+            assert read() == (xcd, window)
+    finally:
+        dg.dg_batch_destroy(b)
+    ctx = dg.dg_create(4, 3, 2, 3, 1.4)
+    try:
+        with pytest.raises(dg.DGError):   # not an option of a single mesh
+            dg.dg_set_option(ctx, dg.DG_OPT_XCD_WINDOW, 0)
+    finally:
+        dg.dg_destroy(ctx)

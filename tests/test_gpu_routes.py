@@ -187,3 +187,32 @@ def test_adjoint_of_small_and_larger_meshes_p7(dgm):
             torch.cuda.synchronize()
         for a, b in zip(*outs):
             assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_batch_deal_of_items_bitwise(dgm, prec):
+    """Windows of items, the plain spread and contiguous parts give the same
+    bits (5000 items of p = 3, 1024 to a window)."""
+    import torch
+    n, p, count = (9, 8, 7), 3, 30
+    print(f"[batch deal {prec}]", flush=True)
+    b = dgm.Batch([n] * count, [p] * count, [(1.0, 1.0, 1.0)] * count,
+                  precision=dgm.DG_FP64 if prec == "fp64" else dgm.DG_FP32_MFMA)
+    assert b.options()["xcd_remap"] == 0 and b.options()["xcd_window"] == 1
+    q = torch.from_numpy(W.random_smooth(n, p, seed=9, noise=0.02)).cuda()
+    Q0 = b.empty()
+    for i in range(count):
+        b.view(Q0, i).copy_(q * (1.0 + 0.001 * i))
+    b.set_dt([1e-3] * count)
+    outs = []
+    for xcd, window in ((0, 1), (0, 0), (1, 0), (1, 1)):
+        b.set_option(dgm.DG_OPT_XCD_REMAP, xcd)
+        b.set_option(dgm.DG_OPT_XCD_WINDOW, window)
+        assert b.options()["xcd_remap"] == xcd and b.options()["xcd_window"] == window
+        Q, res = Q0.clone(), torch.zeros_like(Q0)
+        b.step(Q, res, nsteps=2)
+        torch.cuda.synchronize()
+        outs.append((Q, res))
+    assert bool(torch.isfinite(outs[0][0]).all())
+    for o in outs[1:]:
+        assert torch.equal(o[0], outs[0][0]) and torch.equal(o[1], outs[0][1])
