@@ -224,8 +224,10 @@ int dg_rhs(dg_ctx* ctx, const double* Q, double* R);
 int dg_rk_stage(dg_ctx* ctx, int s, double* Q, double* res, double dt);
 
 /* The same stage out of place: Qnext = Q + b_s res, Q unchanged (for callers
- * that keep every stage's input, as a reverse pass does: no copy of the state
- * is made before or after).  Qnext must not overlap Q or res. */
+ * that keep every stage's input, as a reverse pass does).  One launch without
+ * a copy of the state; with viscosity or DG_EXCHANGE_TRACES (standard form),
+ * whose stages update in place, the state is copied to Qnext first.  Qnext
+ * must not overlap Q or res. */
 int dg_rk_stage_to(dg_ctx* ctx, int s, const double* Q, double* Qnext, double* res, double dt);
 
 /* One LSERK45 time step (five stages) in place. */

@@ -805,8 +805,12 @@ int dg_rk_stage_to(dg_ctx* c, int s, const double* Q, double* Qnext, double* res
   if (rc) return rc;
   rc = check_state_pair(c, Q, "Q", Qnext, "Qnext");
   if (rc) return rc;
-  if (c->exchange == DG_EXCHANGE_NEIGHBOUR && c->mu == 0.0 && c->volume_form == DG_VOLUME_STANDARD) {
-    const int err = timed(c, s == 0 ? TK_STAGE_FIRST : TK_STAGE, [&] { return launch_nb(c, s, Q, Qnext, res, dt); });
+  const bool split = c->volume_form == DG_VOLUME_KEP;
+  if (c->mu == 0.0 && (split || c->exchange == DG_EXCHANGE_NEIGHBOUR)) {
+    const int err = timed(c, s == 0 ? TK_STAGE_FIRST : TK_STAGE, [&] {
+      return split ? dg_launch_split(c, Q, Qnext, res, s == 0 ? 2 : 1, kRKA[s], kRKB[s], dt)
+                   : launch_nb(c, s, Q, Qnext, res, dt);
+    });
     return err ? hip_fail(err, "stage launch") : DG_OK;
   }
   const int err = (int)hipMemcpyAsync(Qnext, Q, state_bytes(c), hipMemcpyDeviceToDevice, c->stream);

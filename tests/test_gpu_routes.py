@@ -216,3 +216,22 @@ def test_batch_deal_of_items_bitwise(dgm, prec):
     assert bool(torch.isfinite(outs[0][0]).all())
     for o in outs[1:]:
         assert torch.equal(o[0], outs[0][0]) and torch.equal(o[1], outs[0][1])
+
+
+@pytest.mark.parametrize("form", ["euler", "fp32", "kep"])
+def test_stage_to_is_one_launch(dgm, form):
+    """The out-of-place stage leaves the workspace, the second state buffer
+    included, as it was."""
+    import torch
+    n, p = (5, 4, 6), 3
+    print(f"[stage to {form}]", flush=True)
+    s = dgm.Solver(n, p, precision=dgm.DG_FP32_MFMA if form == "fp32" else dgm.DG_FP64,
+                   volume_form=dgm.DG_VOLUME_KEP if form == "kep" else dgm.DG_VOLUME_STANDARD)
+    Q = torch.from_numpy(W.random_smooth(n, p, seed=6, noise=0.02)).cuda()
+    Q0, res, nxt = Q.clone(), torch.zeros_like(Q), torch.empty_like(Q)
+    s.rhs(Q)   # (the call below uses the context's stream)
+    s.workspace.fill_(0xa5)
+    dgm.dg_rk_stage_to(s.ctx, 0, Q, nxt, res, 1e-4)
+    torch.cuda.synchronize()
+    assert torch.equal(Q, Q0) and not torch.equal(nxt, Q0)
+    assert bool((s.workspace == 0xa5).all())
