@@ -82,3 +82,12 @@ def test_batch_window_option():
             dg.dg_set_option(ctx, dg.DG_OPT_XCD_WINDOW, 0)
     finally:
         dg.dg_destroy(ctx)
+
+
+def test_variable_degree_lists_beyond_the_cache(tmp_path):
+    """The element lists of meshes whose arrays exceed the last-level cache
+    are partitions by (degree, size), wide, thin and flat meshes, refined and
+    not."""
+    from paper_2006_15698_amd import dg
+    libdir = os.path.dirname(dg.LIB_PATH)
+    _run(tmp_path, "varp_list_check", ("-L", libdir, "-ldg", f"-Wl,-rpath,{libdir}"))
