@@ -147,11 +147,14 @@ inline int dg_pencil_depth(const dg_ctx* c, bool line) {
 // has few blocks (4x4x1024 p=3 47.5 / 34.3, 8x8x512 p=3 87.7 / 63.2).
 //
 // A plane of few blocks gives an XCD next to nothing of its own neighbours:
-// from 48 blocks down (6 per XCD) they share up to 512 blocks of whole slabs
+// below `thin` blocks (6 per XCD) they share up to 512 blocks of whole slabs
 // (a plane / 512 blocks: 4x4x8192 p=3, 4 blocks, 354 / 265; 8x8x2048 p=3, 16
 // blocks, 313 / 268; 12x12x300 p=3, 36 blocks, 102 / 96; above, 100x2x300
-// p=3, 50 blocks, 126 / 130; 12x12x300 p=4, 72 blocks, 203 / 212).
-inline DGOrder dg_order(const dg_ctx* c, int epb, unsigned* grid, bool line = false) {
+// p=3, 50 blocks, 126 / 130; 12x12x300 p=4, 72 blocks, 203 / 212).  The
+// adjoint's kernels, of which a CU holds one to three workgroups, do so only
+// below 16 blocks (16x1x4096 p=3, 4 blocks, 206 / 193, p=5, 16 blocks, 1117 /
+// 1165, 4x4x1024 p=6, 16 blocks, 373 / 416).
+inline DGOrder dg_order(const dg_ctx* c, int epb, unsigned* grid, bool line = false, int thin = 48) {
   DGOrder o;
   const bool pencil = c->order == DG_ORDER_PENCIL;
   const bool hbm = dg_beyond_cache(c);
@@ -172,7 +175,7 @@ inline DGOrder dg_order(const dg_ctx* c, int epb, unsigned* grid, bool line = fa
   *grid = (unsigned)((int64_t)o.nxb * c->ny * c->nz);
   o.slab = o.nxb * c->ny * o.tz;
   o.share = hbm ? o.slab : (int)*grid;
-  if (hbm && o.nxb * c->ny < 48 && o.slab < 512) o.share = o.slab * (512 / o.slab);
+  if (hbm && o.nxb * c->ny < thin && o.slab < 512) o.share = o.slab * (512 / o.slab);
   if (o.share > (int)*grid) o.share = (int)*grid;
   o.full = (int)(*grid / (unsigned)o.share);
   o.q = o.share >> 3;

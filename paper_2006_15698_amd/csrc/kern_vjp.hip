@@ -635,7 +635,7 @@ int launch_vjp_n(const dg_ctx* c, const double* Q, const double* gR, double* gQ,
 template <int N>
 int launch_vjp_nb_n(const dg_ctx* c, const double* Q, const double* gR, double* gQ, double* gres, double a, double dt) {
   unsigned grid;
-  const DGOrder ord = dg_order(c, VCfg<N>::EPB, &grid);
+  const DGOrder ord = dg_order(c, VCfg<N>::EPB, &grid, false, 16);
   const dim3 blk(VCfg<N>::NT);
   if (gres)
     hipLaunchKernelGGL((k_vjp_nb<N, true>), dim3(grid), blk, 0, c->stream, c->tab, Q, gR, gQ, gres, a, dt, ord);
@@ -654,7 +654,7 @@ int dg_launch_vjp_line(const dg_ctx* c, const double* Q, const double* g, double
 // Neighbour reads: the product into gQ, or with gres the reverse stage.
 static int launch_vjp_neighbour(const dg_ctx* c, const double* Q, const double* gR, double* gQ, double* gres, double a,
                                 double dt) {
-  if (dg_vjp_line_pays(c)) return dg_launch_vjp_line(c, Q, gR, gQ, gres, a, dt);
+  if (dg_vjp_line_pays(c, gres != nullptr)) return dg_launch_vjp_line(c, Q, gR, gQ, gres, a, dt);
   switch (c->N) {
     case 1: return launch_vjp_nb_n<1>(c, Q, gR, gQ, gres, a, dt);
     case 2: return launch_vjp_nb_n<2>(c, Q, gR, gQ, gres, a, dt);

@@ -323,7 +323,7 @@ k_vjp_line(DGTables tb, const double* __restrict__ Q, const double* __restrict__
 template <int N>
 int launch_n(const dg_ctx* c, const double* Q, const double* g, double* G, double* gres, double a, double dt) {
   unsigned grid;
-  const DGOrder ord = dg_order(c, 1, &grid, true);
+  const DGOrder ord = dg_order(c, 1, &grid, true, 16);
   if (gres)
     hipLaunchKernelGGL((k_vjp_line<N, true>), dim3(grid), dim3(192), 0, c->stream, c->tab, Q, g, G, gres, a, dt, ord);
   else

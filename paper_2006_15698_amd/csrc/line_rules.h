@@ -43,10 +43,11 @@ inline bool dg_stage_line_pays(const dg_ctx* c) {
   // cache: 16^3, 1024 waves, 12.2 / 13.7, 21^3 25.7 / 23.8, 24^3 32.9 / 31.4,
   // 28^3 47.5 / 46.8, from 30^3 on 58.9 / 59.6).
   if (N == 4 && waves > 2048 && waves <= 6144 && dg_rows_filled(c, 4, 90) && !dg_beyond_cache(c)) return false;
-  // N = 8: one wave per SIMD, 1024 at once; up to four rounds a last one that
+  // N = 8: one wave per SIMD, 1024 at once; up to three rounds a last one that
   // is nearly empty costs what the lines gain (10^3 24.4 / 29.6, 5x16x16
-  // 37.9 / 34.9, 13^3 5%, 16^3 95 / 96; 17x16x17 12% ahead).
-  if (N == 8 && waves > 1024 && waves <= 4096) return false;
+  // 37.9 / 34.9, 13x13x12 5% and 14x14x13 7% behind, 15x15x16 even, 1x64x64 77 /
+  // 87, 17x16x17 12% ahead).
+  if (N == 8 && waves > 1024 && waves <= 3072) return false;
   return true;
 }
 
@@ -60,12 +61,14 @@ inline bool dg_split_line_pays(const dg_ctx* c) {
     case 3: return nx > 1 || waves <= 512;    // 1x64x64 25.2 / 18.3, 1x39x39 18% behind, 1x24x24 even; 2x39x39 0.93
     case 4:
       // 9^3 10.4 / 9.3, 12x10x11 12.6 / 13.1; rows of one or two elements
-      // 1x64x64 33.1 / 24.0, 2x35x35 13% behind, 2x45x45 13% ahead; 3x20x20 even
-      return waves > 384 && nx > 1 && (nx > 2 || waves > 1536);
+      // 1x64x64 33.1 / 24.0, 2x35x35 13% behind, 2x45x45, not yet a second round,
+      // 13% ahead, 2x48x48 27.3 / 25.2, 2x77x77 2% ahead; 3x20x20 even
+      return waves > 384 && nx > 1 && (nx > 2 || (waves > 1536 && waves <= 2048) || waves > 4096);
     case 5:
       // 10^3 15.4 / 13.8, 11^3 16.5 / 16.4, 12^3 17.3 / 18.4; with half-empty
-      // blocks 1x64x64 40.6 / 33.0, 3x20x20 16.2 / 14.5, 3x45x45 even
-      return waves > 704 && nx > 1 && (nx != 3 || waves > 4096);
+      // blocks 1x64x64 40.6 / 33.0, 3x20x20 16.2 / 14.5, 3x45x45 even; just over
+      // the 2048 waves of one round 2x48x48 38 / 36, 18x17x17 5% ahead again
+      return waves > 704 && nx > 1 && (nx != 3 || waves > 4096) && !(waves > 2048 && waves <= 2400);
     case 6: return waves > 512;   // 8^3 16.6 / 14.8, 9x8x8 17.8 / 19.0
     case 7: return waves > 384;   // 7x7x8 18.2 / 19.0 at 392
     default: return waves > 512;  // 8^3 24.9 / 22.8, 9x8x8 26.1 / 31.5
@@ -92,8 +95,8 @@ inline bool dg_visc_line_pays(const dg_ctx* c) {
       return waves > 640 && (cached ? dg_rows_filled(c, 4, 85) : nx > 2);
     case 5:
       // 11x10x10 29.9 / 28.9, 10x11x12 30.7 / 32.1; 3x45x45 12%, 5x35x35 and
-      // 7x17x17 5% behind; beyond the cache 3x103x103 22% ahead, 1x126x126 6% behind
-      return waves > 600 && (cached ? dg_rows_filled(c, 2, 90) : nx > 1);
+      // 7x17x17 and 9x15x15 5% behind; beyond the cache 3x103x103 22% ahead, 1x126x126 6% behind
+      return waves > 600 && (cached ? dg_rows_filled(c, 2, 92) : nx > 1);
     // a block's 36 lines leave two fifths of the lanes idle: 17^2x18 140 / 137, 18^2x19 162 / 180
     case 6: return waves > 5632;
     case 7: return waves > 512;    // 8x7x8 32.5 / 32.7 at 448, 9^3 44 / 48
@@ -129,6 +132,9 @@ inline bool dg_varp_line_pays(int N, int count) {
 // 32^3 p=5 657 / 583): the transposed Lax-Friedrichs Jacobians hold both, and it
 // too forms them one face point a thread.  At N = 7 and 8 its LDS (95 and 139 KB
 // an element) leaves one workgroup on a CU (24^3 p=6 341 / 581, 24^3 p=7 779 /
-// 1781); at N = 8 it is ahead while there is no more than half of one (4^3 19.1 /
-// 17.5, 5^3 19.7 / 17.6, 180 elements 22.0 / 26.3; N = 7 4^3 even).
-inline bool dg_vjp_line_pays(const dg_ctx* c) { return c->N == 7 || (c->N == 8 && c->E > 128); }
+// 1781); at N = 8 it is ahead in the product while there is no more than half of
+// one (4^3 19.1 / 17.5, 5^3 19.7 / 17.6, 180 elements 22.0 / 26.3; N = 7 4^3 even),
+// but not in the reverse stage (4^3 24.2 / 28.8).
+inline bool dg_vjp_line_pays(const dg_ctx* c, bool reverse_stage) {
+  return c->N == 7 || (c->N == 8 && (reverse_stage || c->E > 128));
+}

@@ -79,6 +79,14 @@ int main() {
             m.ny, m.nz, m.N, line, o.share, o.slab);
       CHECK(covers(c, o, grid, epb), "%dx%dx%d N=%d line=%d", m.nx, m.ny, m.nz, m.N, line);
     }
+  // the adjoint's limit
+  for (int nx : {16, 15}) {
+    const dg_ctx c = mesh(nx, 1, 4096, 6);
+    unsigned grid;
+    const DGOrder o = dg_order(&c, 1, &grid, false, 16);
+    CHECK(nx < 16 ? o.share > 256 : o.share == o.slab, "%dx1x4096 share %d slab %d", nx, o.share, o.slab);
+    CHECK(covers(c, o, grid, 1), "%dx1x4096", nx);
+  }
   // state stores marked as not reused: only where state in and out leave
   // nothing of the new one in the cache, at every degree alike
   {
