@@ -305,7 +305,10 @@ dg_varp* build(int nx, int ny, int nz, const int* refine, const int* degrees, co
     // of their parts come from HBM once (us a stage: 40^3 cells of degrees 3..5,
     // the p = 4 group 267 before, 252 so, the p = 5 group 305 and 294; 48^3
     // p = 4 638 and 613; within the cache nothing gained, 32^3 p = 3 72 and 74).
-    const bool hbm = 15 * (int64_t)sizeof(double) * T > ((int64_t)256 << 20);
+    // Planes of few cells give a part next to nothing of an element's own
+    // neighbours, so there the order stays whole (4x4x8192 cells, p = 3 346 and
+    // 297, p = 4 701 and 620; 2x2x2048, p = 6 121 and 105, p = 7 210 and 200).
+    const bool hbm = 15 * (int64_t)sizeof(double) * T > ((int64_t)256 << 20) && nx * ny >= 48;
     const int parts = hbm ? 8 : 1;
     const int px = std::min(kPencilX, nx), pz = hbm ? 1 : std::min(kPencilZ, nz);
     constexpr int GROUPS = (DG_VARP_MAXN + 1) * 2;
