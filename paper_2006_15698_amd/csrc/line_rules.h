@@ -40,9 +40,9 @@ inline bool dg_stage_line_pays(const dg_ctx* c) {
   if (waves <= 512) return false;
   // N = 4: 2048 waves are resident at once; a second round of them ends well
   // after the node kernel's workgroups, of which more fit (full rows in the
-  // cache: 16^3, 1024 waves, 12.2 / 13.7, 21^3 25.7 / 23.8, 24^3 32.9 / 31.4,
-  // 28^3 47.5 / 46.8, from 30^3 on 58.9 / 59.6).
-  if (N == 4 && waves > 2048 && waves <= 6144 && dg_rows_filled(c, 4, 90) && !dg_beyond_cache(c)) return false;
+  // cache: 16^3, 1024 waves, 12.2 / 13.7, 21^3 25.7 / 23.8, 24^3 32.9 / 31.4;
+  // 28^3, 5488 waves, even, 30^3 58.9 / 59.6).
+  if (N == 4 && waves > 2048 && waves <= 4608 && dg_rows_filled(c, 4, 90) && !dg_beyond_cache(c)) return false;
   // N = 8: one wave per SIMD, 1024 at once; up to three rounds a last one that
   // is nearly empty costs what the lines gain (10^3 24.4 / 29.6, 5x16x16
   // 37.9 / 34.9, 13x13x12 5% and 14x14x13 7% behind, 15x15x16 even, 1x64x64 77 /

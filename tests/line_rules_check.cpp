@@ -39,7 +39,7 @@ int main() {
          {"", 3, 1, 1, 1, true}, {"", 3, 8, 8, 8, true}, {"", 3, 9, 30, 30, true}, {"", 3, 28, 28, 28, true},
          {"", 3, 40, 40, 40, true}, {"", 3, 45, 45, 45, true}, {"", 3, 8, 8, 2048, true},
          {"", 4, 8, 16, 16, false}, {"", 4, 12, 14, 14, true}, {"", 4, 16, 16, 32, true}, {"", 4, 16, 16, 33, false},
-         {"", 4, 24, 24, 24, false}, {"", 4, 28, 28, 28, false}, {"", 4, 32, 32, 24, false}, {"", 4, 30, 30, 30, true},
+         {"", 4, 24, 24, 24, false}, {"", 4, 26, 26, 25, false}, {"", 4, 24, 26, 26, false}, {"", 4, 28, 28, 28, true}, {"", 4, 30, 30, 30, true},
          {"", 4, 32, 32, 32, true}, {"", 4, 1, 64, 64, true}, {"", 4, 9, 37, 37, true}, {"", 4, 48, 48, 48, true},
          {"", 5, 8, 8, 16, false}, {"", 5, 8, 8, 17, true}, {"", 6, 8, 8, 8, false}, {"", 6, 8, 8, 9, true},
          {"", 7, 8, 8, 8, false}, {"", 7, 8, 8, 9, true},

@@ -1,6 +1,6 @@
 // Host check of the variable-degree builder's element lists where the arrays
 // of a stage exceed the last-level cache (each XCD's part of a list takes an
-// eighth of every one-plane slab in turn), compiled with the builder's own
+// eighth of every one-plane slab in turn, but for planes of few cells), compiled with the builder's own
 // source as varp_mesh_check.cpp is.  Every element stands once, in its group's
 // range; a group's elements of one plane and part follow one another; and an
 // eighth of a wide mesh's list holds an eighth of every plane, within one.
@@ -54,6 +54,11 @@ static void check(int nx, int ny, int nz, double refined, int plo, int phi, bool
         ++total[plane[e]];
         ++per[(int64_t)i * 8 / count][plane[e]];
       }
+      // planes of few cells: the order of eight-plane slabs stays whole
+      if (beyond && nx * ny < 48)
+        for (int i = 1; i < count; ++i)
+          CHECK(plane[v->list[first + i]] / 8 >= plane[v->list[first + i - 1]] / 8, "%dx%dx%d N=%d: slab order at %d", nx, ny,
+                nz, N, i);
       // parts of near-equal length: their borders drift by less than one
       // element a plane, here at most a plane's own eighth
       if (beyond && refined == 0.0 && plo == phi && nx * ny >= 64)
