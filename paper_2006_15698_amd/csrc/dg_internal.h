@@ -96,6 +96,11 @@ __host__ __device__ __forceinline__ int dg_quot(int n, DGDiv v) {
 // N^2 lines, and their pairs of y/z neighbour points, in 64 lanes.
 constexpr int dg_line_elems(int N) { return N == 2 ? 16 : N == 3 ? 5 : N == 4 ? 4 : N == 5 ? 2 : 1; }
 
+// How the arrays of a stage compare with the 256 MB last-level cache: within
+// it; the three together beyond it; a state above 144 MiB, so that the next
+// launch finds next to nothing of the new one there; a state above 400 MiB.
+enum { DG_CACHED = 0, DG_BEYOND = 1, DG_STREAMED = 2, DG_HUGE = 3 };
+
 // Order in which a neighbour-read stage launch visits its element blocks
 // (kernel argument).  A block is EPB consecutive elements of one x-row (the
 // last block of a row may be short).  Blocks are visited z-slab by z-slab
@@ -111,7 +116,7 @@ struct DGOrder {
   int share;    // blocks the XCDs share at a time: whole slabs, or all
   int full;     // whole shares
   int q;        // share / 8
-  bool stream;  // the new state is marked as not reused: the next launch finds little of it in the last-level cache
+  int size;     // DG_CACHED .. DG_HUGE
   DGDiv dslab, dq, dpen, drow, dtx;   // by slab, q, and a whole pencil's blocks, blocks per y-row, blocks along x
 };
 
@@ -159,14 +164,8 @@ inline DGOrder dg_order(const dg_ctx* c, int epb, unsigned* grid, bool line = fa
   const bool pencil = c->order == DG_ORDER_PENCIL;
   const bool hbm = dg_beyond_cache(c);
   o.xcd = c->xcd_remap;
-  // Where state in and out exceed the cache by little the next launch still
-  // finds part of the new state there: marked, 131 against 116 us a stage at
-  // 48^3 p=2 (two states 229 MiB), 128 / 113 at 30^3 p=4 (258), 120 / 117 at
-  // 38^3 p=3 (268), 148 / 145 at 22^3 p=6 (278); 161 / 159 at 52^3 p=2 and
-  // 148 / 152 at 26^3 p=5 (290); above, marked is faster: 135 / 138 at 40^3
-  // p=3 and 155 / 160 at 32^3 p=4 (313), 188 / 193 at 24^3 p=6 (362), 534 /
-  // 544 at 48^3 p=4 (1055; 40^3 p=6, 1675, even: 868 / 861).
-  o.stream = dg_stage_bytes(c) / 3 * 2 > ((int64_t)300 << 20);
+  const int64_t state = dg_stage_bytes(c) / 3;
+  o.size = !hbm ? DG_CACHED : state <= ((int64_t)144 << 20) ? DG_BEYOND : state <= ((int64_t)400 << 20) ? DG_STREAMED : DG_HUGE;
   o.nxb = (c->nx + epb - 1) / epb;
   const int px = pencil && c->pencil_x > 0 && c->pencil_x < c->nx ? c->pencil_x : c->nx;
   o.tx = (px + epb - 1) / epb;

@@ -80,6 +80,20 @@ k_stage_nb(DGTables tb, const double* __restrict__ Qin, double* __restrict__ Qou
   dgdev::stage_nb_body<N, MODE, EPB, NT, kLines<N>>(tb, Qin, Qout, RR, rka, rkb, dt, first, e0, ne, smem, threadIdx.x);
 }
 
+// Whether the new state is stored as not reused.  State of 115 MiB, marked /
+// plain: 36^3 p=3 1.12, 24^3 p=5 1.12, 48^3 p=2 1.09, 70^3 p=1 1.09 (105 MiB,
+// 28^3 p=4, 1.16); 134 to 142 MiB 38^3 p=3 1.03, 31^3 p=4 and 22^3 p=6 1.01; 145
+// MiB 39^3 p=3, 26^3 p=5 and 78^3 p=1 0.99, 52^3 p=2 1.01; 156 MiB 40^3 p=3 0.97,
+// 32^3 p=4 and 80^3 p=1 0.98; 48^3 p=4 (527) 535 / 543 us, 40^3 p=5 549 / 561.
+// N = 8, which holds the fewest elements on a CU, gains wherever the stage
+// exceeds the cache (17^3, 96 MiB, 0.95; 19^3, 134, 0.98); N = 7 gains up to
+// 400 MiB (24^3 189 / 194, 28^3 even) and loses from there on (34^3 0.6%, 36^3
+// 0.9, 40^3 1.0, 44^3 0.3, 48^3 0.8%).
+template <int N>
+__device__ __forceinline__ bool stream_state(const DGOrder& o) {
+  return o.size >= (N == 8 ? DG_BEYOND : DG_STREAMED) && !(N == 7 && o.size == DG_HUGE);
+}
+
 // Stage kernel with one thread per line, Qin -> Qout.  At 48^3 p=4 the HBM
 // stream bounds it (stages 2..5: 535 us against 632 with a thread per node;
 // reading and writing its state and residual alone takes 450): taking the
@@ -92,7 +106,7 @@ k_stage_line(DGTables tb, const double* __restrict__ Qin, double* __restrict__ Q
   __shared__ __align__(16) double smem[dgdev::LineSmem<N, EPB>::size];
   const dgdev::Block blk = dgdev::block_of<EPB>(tb, ord, blockIdx.x, gridDim.x);
   dgdev::stage_line_body<N, MODE, EPB>(dgdev::EulerLine<N>{{tb}}, tb, Qin, Qout, RR, rka, rkb, dt, first, blk, smem, threadIdx.x,
-                                      ord.stream);
+                                      stream_state<N>(ord));
 }
 
 // ---- reductions -----------------------------------------------------------

@@ -485,6 +485,16 @@ struct SplitLine {
   }
 };
 
+// Whether the new state is stored as not reused (marked / plain: 36^3 p=3, 114
+// MiB, 1.06, 24^3 p=5 1.04, 48^3 p=2 1.05; 145 MiB 39^3 p=3 and 78^3 p=1 1.00, 26^3
+// p=5 1.01; 40^3 p=3, 156 MiB, 0.98; 48^3 p=4 593 / 596 us).  N = 7 and 8 lose by it
+// above 400 MiB (p=6 36^3 0.7%, 40^3 0.7, 44^3 1.2%; p=7 28^3 1.9%, 40^3 1.7%).
+template <int N>
+__device__ __forceinline__ bool stream_state(const DGOrder& o) {
+  return o.size >= DG_STREAMED && !(N >= 7 && o.size == DG_HUGE);
+}
+
+// N = 3 at three waves a SIMD spills one register (8 bytes of scratch a lane).
 template <int N, int MODE>
 __global__ void __launch_bounds__(64, N == 8 ? 1 : N <= 3 ? 3 : 2)
 k_split_line(DGTables tb, SplitTables st, const double* __restrict__ Qin, double* __restrict__ Qout,
@@ -493,7 +503,7 @@ k_split_line(DGTables tb, SplitTables st, const double* __restrict__ Qin, double
   __shared__ __align__(16) double smem[dgdev::LineSmem<N, EPB>::size];
   const dgdev::Block blk = dgdev::block_of<EPB>(tb, ord, blockIdx.x, gridDim.x);
   dgdev::stage_line_body<N, MODE, EPB>(SplitLine<N>{{tb}, st}, tb, Qin, Qout, RR, a, b, dt, 0, blk, smem, threadIdx.x,
-                                      ord.stream);
+                                      stream_state<N>(ord));
 }
 
 template <int N>

@@ -205,7 +205,7 @@ __device__ __forceinline__ void end_traces(const LineTables<N>& t, const double 
 // volume form `form` (EulerLine; kern_split.hip has another); the other
 // arguments and MODE as for stage_nb_body.  smem: LineSmem<N, EPB>::size doubles.
 // nt: mark the new state as not reused, for states that the next launch would
-// not find in the last-level cache anyway (DGOrder::stream): their stores then
+// not find in the last-level cache anyway (DGOrder::size): their stores then
 // do not push the state that the neighbours read out of the L2.
 template <int N, int MODE, int EPB, class Form>
 __device__ __forceinline__ void stage_line_body(const Form& form, const DGTables& tb, const double* __restrict__ Qin,

@@ -87,18 +87,19 @@ int main() {
     CHECK(nx < 16 ? o.share > 256 : o.share == o.slab, "%dx1x4096 share %d slab %d", nx, o.share, o.slab);
     CHECK(covers(c, o, grid, 1), "%dx1x4096", nx);
   }
-  // state stores marked as not reused: only where state in and out leave
-  // nothing of the new one in the cache, at every degree alike
+  // size classes: three arrays against the cache, then the state alone
   {
-    struct Case { Mesh m; bool stream; };
-    for (Case k : {Case{{36, 36, 36, 4}, false}, Case{{24, 24, 24, 6}, false}, Case{{72, 72, 72, 2}, false},
-                   Case{{48, 48, 48, 3}, false}, Case{{30, 30, 30, 5}, false}, Case{{22, 22, 22, 7}, false},
-                   Case{{40, 40, 40, 4}, true}, Case{{32, 32, 32, 5}, true}, Case{{80, 80, 80, 2}, true},
-                   Case{{48, 48, 48, 5}, true}, Case{{24, 24, 24, 7}, true}, Case{{40, 40, 40, 7}, true}}) {
+    struct Case { Mesh m; int size; };
+    for (Case k : {Case{{32, 32, 32, 4}, DG_CACHED}, Case{{16, 16, 16, 8}, DG_CACHED}, Case{{17, 17, 17, 8}, DG_BEYOND},
+                   Case{{36, 36, 36, 4}, DG_BEYOND}, Case{{24, 24, 24, 6}, DG_BEYOND}, Case{{72, 72, 72, 2}, DG_BEYOND},
+                   Case{{48, 48, 48, 3}, DG_BEYOND}, Case{{31, 31, 31, 5}, DG_BEYOND}, Case{{22, 22, 22, 7}, DG_BEYOND},
+                   Case{{39, 39, 39, 4}, DG_STREAMED}, Case{{26, 26, 26, 6}, DG_STREAMED}, Case{{32, 32, 32, 5}, DG_STREAMED},
+                   Case{{80, 80, 80, 2}, DG_STREAMED}, Case{{24, 24, 24, 7}, DG_STREAMED}, Case{{48, 48, 48, 5}, DG_HUGE},
+                   Case{{36, 36, 36, 7}, DG_HUGE}, Case{{40, 40, 40, 7}, DG_HUGE}}) {
       const dg_ctx c = mesh(k.m.nx, k.m.ny, k.m.nz, k.m.N);
       unsigned grid;
       const DGOrder o = dg_order(&c, dg_line_elems(k.m.N), &grid, true);
-      CHECK(o.stream == k.stream, "%dx%dx%d N=%d stream %d", k.m.nx, k.m.ny, k.m.nz, k.m.N, (int)o.stream);
+      CHECK(o.size == k.size, "%dx%dx%d N=%d size %d", k.m.nx, k.m.ny, k.m.nz, k.m.N, o.size);
     }
   }
   // never more than the launch

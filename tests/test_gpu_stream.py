@@ -16,7 +16,7 @@ def dgm():
 
 
 @pytest.mark.parametrize("p,n", [(2, (56, 55, 50)), (3, (41, 39, 40)), (3, (36, 35, 36)), (4, (4, 8, 1100)),
-                                 (6, (24, 24, 25))])
+                                 (6, (24, 24, 25)), (7, (17, 17, 17))])
 def test_steps_beyond_the_cache_equal_the_trace_exchange(dgm, p, n):
     """Neighbour reads against the trace-buffer kernel (a node per thread,
     index order, plain stores)."""
