@@ -92,7 +92,7 @@ def flops_per_dof_stage(N):
 # neighbour-read adjoint kernel.
 _COMMON_SOURCES = ["paper_2006_15698_amd/csrc/dg_internal.h",
                    "paper_2006_15698_amd/csrc/stage_fp64.h", "paper_2006_15698_amd/csrc/stage_nb.h",
-                   "paper_2006_15698_amd/csrc/stage_line.h"]
+                   "paper_2006_15698_amd/csrc/stage_line.h", "paper_2006_15698_amd/csrc/line_rules.h"]
 _FP32_SOURCES = ["paper_2006_15698_amd/csrc/stage_fp32.h", "paper_2006_15698_amd/csrc/stage_nb32.h"]
 STAGE_SOURCES = {
     "fp64": _COMMON_SOURCES + ["paper_2006_15698_amd/csrc/kern_fp64.hip"],
